@@ -216,6 +216,23 @@ int fotci_apply_H(const fotci_ham *h, int32_t mode, const void *x, void *y, void
 int fotci_apply_H_block(const fotci_ham *h, int32_t mode, int32_t n_block, const void *x, void *y, void *stream);
 
 /*
+ * fotci_apply_H_work -- fotci_apply_H (n_block 1) or fotci_apply_H_block with
+ * device work memory, with which the proton-neutron part runs on faster
+ * kernels: contributions to a row of y from its Z protons are summed in Z
+ * slots of the work memory. work: device memory of at least
+ * fotci_apply_work_bytes(h, mode, n_block) bytes, 16-byte aligned, not
+ * overlapping x or y; it is overwritten and must not be used by other work
+ * until the call's kernels have run on `stream`, and calls that may overlap in
+ * time need one each. NULL (or a query of 0: the basis or mode has no such
+ * kernels) runs the kernels of fotci_apply_H. Arguments, errors and results
+ * otherwise as for those calls; results agree up to rounding order.
+ * FOTCI_ENOMEM if work_bytes is too small.
+ */
+int64_t fotci_apply_work_bytes(const fotci_ham *h, int32_t mode, int32_t n_block);
+int fotci_apply_H_work(const fotci_ham *h, int32_t mode, int32_t n_block, const void *x, void *y, void *work,
+                       int64_t work_bytes, void *stream);
+
+/*
  * fotci_apply_H_vjp_static -- fotci_apply_H_vjp for callers that cannot
  * allocate or must not depend on per-call device memory (code under HIP graph
  * capture, tight serving or training loops, harnesses that forbid hipMalloc).
@@ -269,7 +286,10 @@ typedef struct {
     int32_t reorth;   /* FOTCI_REORTH_* */
 } fotci_lanczos_opts;
 
-/* Bytes of device workspace fotci_lanczos_lowest needs for these options. */
+/* Bytes of device workspace fotci_lanczos_lowest needs for these options (also
+ * the queries below). They end with the work memory of fotci_apply_H_work for
+ * the recurrence and the float64 refinement; a workspace without that part is
+ * accepted and the products then run without it. */
 int64_t fotci_lanczos_workspace_bytes(const fotci_ham *h, const fotci_lanczos_opts *o);
 
 /*
@@ -280,7 +300,8 @@ int64_t fotci_lanczos_workspace_bytes(const fotci_ham *h, const fotci_lanczos_op
  * beta, reorthogonalisation coefficients and the tridiagonal eigenproblem are
  * float64.
  *  pivot: device float64 [dim], the starting vector (normalised internally).
- *  work: device workspace of the queried size (FOTCI_ENOMEM if smaller).
+ *  work: device workspace of the queried size (FOTCI_ENOMEM if smaller, apart
+ *  from its work memory part).
  *  evals, resid: host [n_keep]; resid = ||H y - theta y|| / ||y|| in float64.
  *  evecs: device float64 [n_keep*dim] Ritz vectors (unit norm), or NULL.
  *  alpha, beta: host [n_iter] copies of the recurrence, or NULL.

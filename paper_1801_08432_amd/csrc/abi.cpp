@@ -192,6 +192,42 @@ int fotci_apply_H_block(const fotci_ham *h, int32_t mode, int32_t n_block, const
     });
 }
 
+int64_t fotci_apply_work_bytes(const fotci_ham *h, int32_t mode, int32_t n_block) {
+    int64_t r = 0;
+    const int rc = guard([&] {
+        if (!h) fail(FOTCI_EINVAL, "NULL handle");
+        if (n_block != 1 && n_block != 2 && n_block != 4 && n_block != 8)
+            fail(FOTCI_EINVAL, "n_block must be 1, 2, 4 or 8");
+        r = apply_work_bytes(h, mode, n_block);
+        return FOTCI_OK;
+    });
+    return rc == FOTCI_OK ? r : rc;
+}
+
+int fotci_apply_H_work(const fotci_ham *h, int32_t mode, int32_t n_block, const void *x, void *y, void *work,
+                       int64_t work_bytes, void *stream) {
+    return guard([&] {
+        if (!h || !x || !y) fail(FOTCI_EINVAL, "NULL argument");
+        if (n_block != 1 && n_block != 2 && n_block != 4 && n_block != 8)
+            fail(FOTCI_EINVAL, "n_block must be 1, 2, 4 or 8");
+        if (mode != FOTCI_MODE_F64 && mode != FOTCI_MODE_F32 && !(mode == FOTCI_MODE_F64_PLAIN && n_block == 1))
+            fail(FOTCI_EINVAL, "block apply_H needs FOTCI_MODE_F64 or FOTCI_MODE_F32");
+        if (!h->uploaded) fail(FOTCI_ESTATE, "Hamiltonian not uploaded");
+        const int64_t es = mode == FOTCI_MODE_F32 ? 4 : 8, need = apply_work_bytes(h, mode, n_block);
+        if (need == 0) work = nullptr;
+        if (work && work_bytes < need) fail(FOTCI_ENOMEM, "work smaller than fotci_apply_work_bytes");
+        if (work && ((uintptr_t)work & 15u)) fail(FOTCI_EINVAL, "work must be 16-byte aligned");
+        const int64_t bytes = h->j->b->dim * n_block * es;
+        const char *xa = (const char *)x, *ya = (const char *)y, *wa = (const char *)work;
+        auto overlap = [](const char *a, int64_t na, const char *b, int64_t nb) { return a < b + nb && b < a + na; };
+        if (n_block > 1 ? overlap(xa, bytes, ya, bytes) : xa == ya) fail(FOTCI_EINVAL, "x and y must not overlap");
+        if (wa && (overlap(xa, bytes, wa, need) || overlap(ya, bytes, wa, need)))
+            fail(FOTCI_EINVAL, "work must not overlap x or y");
+        launch_apply_nb(h, mode, n_block, x, y, stream, work);
+        return FOTCI_OK;
+    });
+}
+
 int fotci_apply_H_vjp(const fotci_ham *h, const double *x, const double *g, double *dx, double *d_spe_p,
                       double *d_spe_n, double *d_v_pp, double *d_v_nn, double *d_v_pn, void *stream) {
     return guard([&] {

@@ -146,6 +146,43 @@ struct alignas(4) EllE64 {
     uint32_t v_lo, v_hi;
 };
 
+// Tables of the core kernels (proton-neutron part through SDs with one proton
+// and one neutron removed). A proton (neutron) core is a kept SD with one
+// particle taken out; cores are grouped by (2M, parity). A pair class holds the
+// ordered pairs (proton state a, neutron state b) of one (2m_a + 2m_b, parity).
+// For a proton core u and a pair class the neutron cores that complete the
+// basis quantum numbers are one neutron core group.
+constexpr int kCoreMinShift = 2, kCoreMaxShift = 6;   // byte offset = column << shift: log2(element size * vectors)
+constexpr int kCoreMaxPc = 64;      // pair classes
+constexpr int kCoreStates = 8;      // added states of a work item
+constexpr int kCoreMaxPos = 32;     // positions (a state a with up to four states b) of an item in a class
+constexpr int kCoreRowElems = 14336;   // row elements of a work item in LDS (float64)
+struct DevCore {
+    const uint32_t *u_mask;    // [n_u] proton cores
+    const int32_t *u_group;    // [n_u]
+    const int32_t *u_row;      // [n_u * ns] proton SD u + a, bit 31: phase of a, -1: none
+    const int32_t *w_of;       // [u groups * n_pc] neutron core group, -1: none
+    const int32_t *w_n;        // [w groups] cores
+    const int32_t *w_pad;      // [w groups] cores rounded up to 16
+    const int32_t *w_off;      // [w groups] first code: state b, core j at w_off + b * w_pad + j
+    // neutron column of core + b in its sector, bit 31: phase of b; none (b
+    // occupied, sector dropped, padding core): the table's null code
+    const uint32_t *w_code[kCoreMaxShift - kCoreMinShift + 1];
+    const int32_t *pc_n;       // [n_pc] pairs of the class
+    const int32_t *pc_pair;    // [n_pc] first pair in pair_ab
+    const int32_t *pc_v;       // [n_pc] first element of its n x n block of V
+    const int32_t *pc_first;   // [n_pc * (ns + 1)] first pair (inside the class) of proton state a
+    const int32_t *pair_ab;    // a | b << 8, by a, then b
+    const double *v64;         // V[(a b), (c d)] per class
+    float *v32;
+    const int32_t *items;      // work items {proton core, mask of the added states a}
+    int32_t n_pc, n_w_code, w_null, n_v, ns;   // w_null: first of a run of null codes as long as the largest group
+};
+
+// Code of "no column" for byte shift s: shifted, it lies past any vector
+// (2 GiB) and a row's byte offset added to it does not wrap.
+constexpr uint32_t core_null(int shift) { return 0x80000000u >> shift; }
+
 // Extra device tables of the tiled kernels (indexed by basis sector s; each
 // basis sector owns one proton and one neutron species sector).
 struct DevTiled {
@@ -196,6 +233,19 @@ struct DevTiled {
     int32_t max_nn, max_np;
     int32_t ok;
     int32_t pn_priv;             // float pn kernel: 1 = a private output row per wave when it fits, 0 = shared row
+};
+
+// Host side of DevCore.
+struct HostCore {
+    bool ok = false;
+    int n_pc = 0, w_null = 0;
+    std::vector<uint32_t> u_mask;
+    std::vector<int32_t> u_group, u_row, w_of, w_n, w_pad, w_off, pc_n, pc_pair, pc_v, pc_first, pair_ab;
+    std::vector<uint32_t> w_code[kCoreMaxShift - kCoreMinShift + 1];
+    std::vector<int32_t> v_src;         // index into v_pn of every element of v
+    std::vector<double> v;
+    std::vector<int32_t> items;         // 2 ints each
+    int item_cols = 0;                  // most row elements of an item
 };
 
 // The pn kernel's per-wave tile R holds, for the kPnTile source columns of a
@@ -252,6 +302,8 @@ struct fotci_ham {
     fotci::HostSpeciesTables tp, tn;
     fotci::HostCommonTables tc;
     fotci::HostTiled tt;
+    fotci::HostCore hc;
+    fotci::DevCore dev_core{};
     fotci::DevTiled dev_tiled{};
     int32_t pn_priv = 1;                  // see fotci_ham_set_pn_private_rows
     // device
@@ -282,17 +334,28 @@ void fill_species_values(fotci_ham *h);
 // device helpers (kernels_*.hip)
 void launch_materialize(const fotci_ham *h, void *stream);
 void launch_materialize_tiled(const DevHam &d, const DevTiled &t, void *stream);
-void launch_apply(const fotci_ham *h, int mode, const void *x, void *y, void *stream);
+// work: apply_work_bytes bytes of device memory, or null (the pn part then
+// runs on the one-body-jump kernels, which need none)
+void launch_apply(const fotci_ham *h, int mode, const void *x, void *y, void *stream, void *work = nullptr);
 void launch_apply_plain(const DevHam &d, int mode, const void *x, void *y, void *stream);
-void launch_apply_tiled(const DevHam &d, const DevTiled &t, int mode, const void *x, void *y, void *stream,
-                        void **events = nullptr);
-void launch_apply_block(const DevHam &d, const DevTiled &t, int mode, int nb, const void *x, void *y, void *stream,
-                        void **events = nullptr);
+void launch_apply_tiled(const fotci_ham *h, int mode, const void *x, void *y, void *stream, void **events,
+                        void *work);
+void launch_apply_block(const fotci_ham *h, int mode, int nb, const void *x, void *y, void *stream, void **events,
+                        void *work);
 // pn part of the block apply (nb 2, 4 or 8; adds to y): the one-vector pn kernel with a vector stride
 void launch_pn_block(const DevHam &d, const DevTiled &t, int mode, int nb, const void *x, void *y, void *stream);
 // block apply with the per-kernel timing of launch_apply; nb == 1 is launch_apply
-void launch_apply_nb(const fotci_ham *h, int mode, int nb, const void *x, void *y, void *stream);
+void launch_apply_nb(const fotci_ham *h, int mode, int nb, const void *x, void *y, void *stream, void *work = nullptr);
 void build_tiled_tables(fotci_ham *h);
+// tables of the core kernels (host_cores.cpp); fill: the matrix elements only
+void build_core_tables(fotci_ham *h);
+void fill_core_values(fotci_ham *h);
+// Bytes of work with which apply_H (nb vectors row-wise) runs its pn part on
+// the core kernels, 0 where it does not use them: one slot of dim * nb elements
+// per proton.
+int64_t apply_work_bytes(const fotci_ham *h, int mode, int nb);
+// pn part into the slots
+void launch_pn_cores(const fotci_ham *h, int mode, int nb, const void *x, void *slots, void *stream);
 void launch_one_body_density(const DevHam &d, const std::vector<int32_t> &h_sec_np, int q0, const double *g,
                              const double *x, double *rho_p, double *rho_n, void *stream);
 // ncol: device buffer of n_nsd doubles for the neutron column sums, or NULL

@@ -1,0 +1,200 @@
+// Host tables of the core kernels: the proton-neutron part of H written with
+// one particle of each species taken out and put back,
+//   sum_{abcd} V[(a b),(c d)] (p+_a n+_b) (n_d p_c),
+// so that x is gathered once per (proton core, neutron core) pair for all the
+// pairs (c d) that fill it, one dense matrix V of the pair's (2m, parity)
+// turns them into the pairs (a b), and the results are added to y.
+#include <algorithm>
+#include <map>
+
+#include "fotci_internal.h"
+
+namespace fotci {
+
+namespace {
+
+inline bool odd_below(uint32_t m, int i) { return __builtin_popcount(m & ((1u << i) - 1u)) & 1; }
+
+struct Cores {
+    std::vector<uint32_t> mask;              // grouped by (2M, parity), ascending inside a group
+    std::vector<int32_t> group;
+    std::map<std::pair<int, int>, int> group_of;
+    std::vector<int> first, count;
+};
+
+Cores cores_of(const SpeciesBasis &sb, const std::vector<MState> &ms) {
+    std::vector<uint32_t> all;
+    for (uint32_t m : sb.sd)
+        for (uint32_t r = m; r; r &= r - 1) all.push_back(m & ~(r & (0u - r)));
+    std::sort(all.begin(), all.end());
+    all.erase(std::unique(all.begin(), all.end()), all.end());
+    std::map<std::pair<int, int>, std::vector<uint32_t>> by;
+    for (uint32_t m : all) {
+        int tm = 0, par = 1;
+        for (size_t i = 0; i < ms.size(); ++i)
+            if ((m >> i) & 1u) tm += ms[i].two_m, par *= ms[i].parity;
+        by[{tm, par}].push_back(m);
+    }
+    Cores c;
+    for (auto &g : by) {
+        const int id = (int)c.group_of.size();
+        c.group_of[g.first] = id;
+        c.first.push_back((int)c.mask.size());
+        c.count.push_back((int)g.second.size());
+        for (uint32_t m : g.second) c.mask.push_back(m), c.group.push_back(id);
+    }
+    return c;
+}
+
+}  // namespace
+
+void build_core_tables(fotci_ham *h) {
+    const fotci_basis *b = h->j->b;
+    const auto &ms = b->ms;
+    const int ns = h->j->ns;
+    HostCore &t = h->hc;
+    t = HostCore();
+    if (b->p.n < 1 || b->n.n < 1 || !h->tt.ok) return;
+    const Cores U = cores_of(b->p, ms), W = cores_of(b->n, ms);
+    t.u_mask = U.mask;
+    t.u_group = U.group;
+    // kept SD by mask, per species
+    auto index = [](const SpeciesBasis &sb) {
+        std::vector<std::pair<uint32_t, int32_t>> v(sb.sd.size());
+        for (size_t i = 0; i < sb.sd.size(); ++i) v[i] = {sb.sd[i], (int32_t)i};
+        std::sort(v.begin(), v.end());
+        return v;
+    };
+    auto find = [](const std::vector<std::pair<uint32_t, int32_t>> &v, uint32_t m) {
+        auto it = std::lower_bound(v.begin(), v.end(), std::make_pair(m, (int32_t)0));
+        return it != v.end() && it->first == m ? it->second : -1;
+    };
+    const auto pidx = index(b->p), nidx = index(b->n);
+    t.u_row.assign(U.mask.size() * (size_t)ns, -1);
+    for (size_t u = 0; u < U.mask.size(); ++u)
+        for (int a = 0; a < ns; ++a) {
+            if ((U.mask[u] >> a) & 1u) continue;
+            const int ip = find(pidx, U.mask[u] | (1u << a));
+            if (ip >= 0) t.u_row[u * ns + a] = ip | (odd_below(U.mask[u], a) ? (int32_t)0x80000000u : 0);
+        }
+    // neutron cores: groups, codes
+    const int nw = (int)W.count.size();
+    int64_t total = 0;
+    for (int g = 0; g < nw; ++g) {
+        t.w_n.push_back(W.count[g]);
+        t.w_pad.push_back((W.count[g] + 15) & ~15);
+        t.w_off.push_back((int32_t)total);
+        total += (int64_t)t.w_pad.back() * ns;
+    }
+    t.w_null = (int)total;   // a run of null codes as long as the largest group
+    total += *std::max_element(t.w_pad.begin(), t.w_pad.end());
+    if (total * 4 >= ((int64_t)1 << 30)) return;
+    for (int s = kCoreMinShift; s <= kCoreMaxShift; ++s) t.w_code[s - kCoreMinShift].assign((size_t)total, core_null(s));
+    for (int g = 0; g < nw; ++g)
+        for (int j = 0; j < W.count[g]; ++j) {
+            const uint32_t m = W.mask[W.first[g] + j];
+            for (int d = 0; d < ns; ++d) {
+                if ((m >> d) & 1u) continue;
+                const int jn = find(nidx, m | (1u << d));
+                if (jn < 0) continue;
+                const uint32_t code = (uint32_t)b->n.sd_local[jn] | (odd_below(m, d) ? 0x80000000u : 0u);
+                for (auto &c : t.w_code) c[(size_t)t.w_off[g] + (size_t)d * t.w_pad[g] + j] = code;
+            }
+        }
+    // a code's column shifted must stay below the null code's bit
+    if (h->tt.max_nn >= (1 << (31 - kCoreMaxShift))) return;
+    // pair classes
+    std::map<std::pair<int, int>, std::vector<std::pair<int, int>>> pcs;
+    for (int a = 0; a < ns; ++a)
+        for (int c = 0; c < ns; ++c) pcs[{ms[a].two_m + ms[c].two_m, ms[a].parity * ms[c].parity}].push_back({a, c});
+    const size_t ns2 = (size_t)ns * ns;
+    std::vector<std::pair<int, int>> pc_q;   // most pairs first: the tasks of a workgroup are drawn in this order
+    for (auto &pc : pcs) pc_q.push_back(pc.first);
+    std::stable_sort(pc_q.begin(), pc_q.end(), [&](const auto &x, const auto &y) { return pcs[x].size() > pcs[y].size(); });
+    for (auto &q : pc_q) {
+        const auto &pr = pcs[q];   // by a, then b
+        t.pc_n.push_back((int32_t)pr.size());
+        t.pc_pair.push_back((int32_t)t.pair_ab.size());
+        t.pc_v.push_back((int32_t)t.v_src.size());
+        size_t k = 0;
+        for (int a = 0; a <= ns; ++a) {
+            while (k < pr.size() && pr[k].first < a) ++k;
+            t.pc_first.push_back((int32_t)k);
+        }
+        for (auto &p : pr) t.pair_ab.push_back(p.first | (p.second << 8));
+        for (auto &p : pr)
+            for (auto &r : pr)
+                t.v_src.push_back((int32_t)(((size_t)p.first * ns + p.second) * ns2 + (size_t)r.first * ns + r.second));
+    }
+    t.n_pc = (int)t.pc_n.size();
+    const int nu = (int)U.count.size();
+    t.w_of.assign((size_t)nu * t.n_pc, -1);
+    for (auto &g : U.group_of)
+        for (int k = 0; k < t.n_pc; ++k) {
+            auto it = W.group_of.find({b->two_M - g.first.first - pc_q[k].first, b->parity * g.first.second * pc_q[k].second});
+            if (it != W.group_of.end()) t.w_of[(size_t)g.second * t.n_pc + k] = it->second;
+        }
+    if (t.n_pc > kCoreMaxPc || t.v_src.size() * 8 >= (1u << 30)) return;
+    // Work items: a core with as many of the states a as a workgroup takes
+    // (rows in LDS); the costliest start first.
+    int most = 0;   // positions of an item in a class
+    struct It {
+        int u;
+        uint32_t amask;
+        int64_t cost;
+    };
+    std::vector<It> its;
+    for (int u = 0; u < (int)U.mask.size(); ++u) {
+        std::vector<std::pair<int, int>> st;   // (state, row columns)
+        int64_t all = 0;
+        for (int a = 0; a < ns; ++a) {
+            const int32_t row = t.u_row[(size_t)u * ns + a];
+            if (row == -1) continue;
+            st.push_back({a, b->sectors[b->p_basis_sector[row & 0x7fffffff]].nn});
+            all += st.back().second;
+        }
+        // as few items as fit, of about equal size
+        const int64_t parts = std::max<int64_t>({1, (all + kCoreRowElems - 1) / kCoreRowElems,
+                                                 ((int64_t)st.size() + kCoreStates - 1) / kCoreStates});
+        const size_t aim = (st.size() + (size_t)parts - 1) / (size_t)parts;
+        uint32_t am = 0;
+        int64_t cols = 0;
+        auto emit = [&] {
+            if (!am) return;
+            int64_t cost = 0;
+            for (int p = 0; p < t.n_pc; ++p) {
+                const int w = t.w_of[(size_t)U.group[u] * t.n_pc + p];
+                if (w < 0) continue;
+                cost += (int64_t)t.w_pad[w] * t.pc_n[p] + 4096;
+                int pos = 0;
+                for (int a = 0; a < ns; ++a)
+                    if ((am >> a) & 1u)
+                        pos += (t.pc_first[(size_t)p * (ns + 1) + a + 1] - t.pc_first[(size_t)p * (ns + 1) + a] + 3) / 4;
+                most = std::max(most, pos);
+            }
+            its.push_back({u, am, cost * (4 + __builtin_popcount(am))});
+            t.item_cols = std::max(t.item_cols, (int)cols);
+            am = 0;
+            cols = 0;
+        };
+        for (auto &s : st) {
+            if (am && cols + s.second > kCoreRowElems) emit();
+            am |= 1u << s.first;
+            cols += s.second;
+            if ((size_t)__builtin_popcount(am) >= aim) emit();
+        }
+        emit();
+    }
+    if (most > kCoreMaxPos) return;
+    std::stable_sort(its.begin(), its.end(), [](const It &x, const It &y) { return x.cost > y.cost; });
+    for (auto &i : its) t.items.push_back(i.u), t.items.push_back((int32_t)i.amask);
+    t.ok = true;
+}
+
+void fill_core_values(fotci_ham *h) {
+    HostCore &t = h->hc;
+    t.v.resize(t.v_src.size());
+    for (size_t i = 0; i < t.v.size(); ++i) t.v[i] = h->v_pn[t.v_src[i]];
+}
+
+}  // namespace fotci

@@ -360,6 +360,7 @@ void fill_species_values(fotci_ham *h) {
         t.v2 = sp == 0 ? h->v_pp : h->v_nn;
     }
     block_pn(h);
+    fill_core_values(h);
 }
 
 namespace {
@@ -512,6 +513,30 @@ std::vector<Item> items(fotci_ham *h) {
     add(tt.pn2_ptr.data(), tt.pn2_ptr.size() * 4, &dt.pn2_ptr);
     add(tt.pn_ndiag.data(), tt.pn_ndiag.size(), &dt.pn_ndiag);
     add(tt.pn2_code.data(), tt.pn2_code.size() * 4, &dt.pn2_code);
+    HostCore &hc = h->hc;
+    DevCore &dc = h->dev_core;
+    dc.n_pc = hc.n_pc;
+    dc.ns = h->j->ns;
+    dc.n_w_code = (int32_t)hc.w_code[0].size();
+    dc.w_null = hc.w_null;
+    dc.n_v = (int32_t)hc.v_src.size();
+    add(hc.u_mask.data(), hc.u_mask.size() * 4, &dc.u_mask);
+    add(hc.u_group.data(), hc.u_group.size() * 4, &dc.u_group);
+    add(hc.u_row.data(), hc.u_row.size() * 4, &dc.u_row);
+    add(hc.w_of.data(), hc.w_of.size() * 4, &dc.w_of);
+    add(hc.w_n.data(), hc.w_n.size() * 4, &dc.w_n);
+    add(hc.w_pad.data(), hc.w_pad.size() * 4, &dc.w_pad);
+    add(hc.w_off.data(), hc.w_off.size() * 4, &dc.w_off);
+    for (int s = 0; s <= kCoreMaxShift - kCoreMinShift; ++s)
+        add(hc.w_code[s].data(), hc.w_code[s].size() * 4, &dc.w_code[s]);
+    add(hc.pc_n.data(), hc.pc_n.size() * 4, &dc.pc_n);
+    add(hc.pc_pair.data(), hc.pc_pair.size() * 4, &dc.pc_pair);
+    add(hc.pc_v.data(), hc.pc_v.size() * 4, &dc.pc_v);
+    add(hc.pc_first.data(), hc.pc_first.size() * 4, &dc.pc_first);
+    add(hc.pair_ab.data(), hc.pair_ab.size() * 4, &dc.pair_ab);
+    add(hc.v.data(), hc.v_src.size() * 8, &dc.v64);
+    add(nullptr, hc.v_src.size() * 4, &dc.v32);
+    add(hc.items.data(), hc.items.size() * 4, &dc.items);
     for (int sp = 0; sp < 2; ++sp) {
         HostSpeciesTables &t = sp == 0 ? h->tp : h->tn;
         DevSpecies &ds = sp == 0 ? d.p : d.n;
@@ -569,6 +594,7 @@ extern "C" int fotci_set_interaction_impl(const fotci_jumps *j, const double *sp
         build_species_tables(j, 0, h->tp);
         build_species_tables(j, 1, h->tn);
         build_tiled_tables(h);
+        build_core_tables(h);
         fill_species_values(h);
         fill_dev_scalars(h);
         int64_t off = 0;
@@ -617,6 +643,9 @@ extern "C" int fotci_ham_set_values_impl(fotci_ham *h, const double *spe_p, cons
         hipStream_t st = (hipStream_t)stream;
         hip_check(hipMemcpyAsync((void *)h->dev.vq64, h->vq.data(), h->vq.size() * 8, hipMemcpyHostToDevice, st),
                   "upload");
+        if (!h->hc.v.empty())
+            hip_check(hipMemcpyAsync((void *)h->dev_core.v64, h->hc.v.data(), h->hc.v.size() * 8,
+                                     hipMemcpyHostToDevice, st), "upload");
         for (int sp = 0; sp < 2; ++sp) {
             HostSpeciesTables &t = sp == 0 ? h->tp : h->tn;
             DevSpecies &ds = sp == 0 ? h->dev.p : h->dev.n;

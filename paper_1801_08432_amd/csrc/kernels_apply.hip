@@ -139,6 +139,9 @@ void launch_materialize(const fotci_ham *h, void *stream) {
     }
     if (d.n_vq > 0)
         hipLaunchKernelGGL(k_to_f32, dim3(blocks_for(d.n_vq, 256)), dim3(256), 0, st, d.vq64, d.vq32, d.n_vq);
+    if (h->dev_core.n_v > 0)
+        hipLaunchKernelGGL(k_to_f32, dim3(blocks_for(h->dev_core.n_v, 256)), dim3(256), 0, st, h->dev_core.v64,
+                           h->dev_core.v32, h->dev_core.n_v);
     hip_check(hipGetLastError(), "materialize launch");
     launch_materialize_tiled(d, h->dev_tiled, stream);
 }
@@ -156,7 +159,7 @@ void launch_apply_plain(const DevHam &d, int mode, const void *x, void *y, void 
     hip_check(hipGetLastError(), "apply launch");
 }
 
-void launch_apply(const fotci_ham *h, int mode, const void *x, void *y, void *stream) {
+void launch_apply(const fotci_ham *h, int mode, const void *x, void *y, void *stream, void *work) {
     auto &pr = h->prof;
     void **ev = nullptr;
     if (pr.on && pr.calls < pr.max_calls) ev = &pr.events[(size_t)pr.calls * 5];
@@ -172,12 +175,11 @@ void launch_apply(const fotci_ham *h, int mode, const void *x, void *y, void *st
             break;
         case FOTCI_MODE_F64:
         case FOTCI_MODE_F32:
-            launch_apply_tiled(h->dev, h->dev_tiled, mode, x, y, stream, ev);
+            launch_apply_tiled(h, mode, x, y, stream, ev, work);
             if (ev) {
                 pr.n_kernels = 3;
-                pr.names[0] = "k_nn_diag";
-                pr.names[1] = "k_pp";
-                pr.names[2] = "k_pn";
+                static const char *const order[2][3] = {{"k_nn_diag", "k_pp", "k_pn"}, {"k_pn", "k_nn_diag", "k_pp"}};
+                for (int k = 0; k < 3; ++k) pr.names[k] = order[work ? 1 : 0][k];
             }
             break;
         default:
@@ -186,20 +188,19 @@ void launch_apply(const fotci_ham *h, int mode, const void *x, void *y, void *st
     if (ev) pr.calls++;
 }
 
-void launch_apply_nb(const fotci_ham *h, int mode, int nb, const void *x, void *y, void *stream) {
+void launch_apply_nb(const fotci_ham *h, int mode, int nb, const void *x, void *y, void *stream, void *work) {
     if (nb == 1) {
-        launch_apply(h, mode, x, y, stream);
+        launch_apply(h, mode, x, y, stream, work);
         return;
     }
     auto &pr = h->prof;
     void **ev = nullptr;
     if (pr.on && pr.calls < pr.max_calls) ev = &pr.events[(size_t)pr.calls * 5];
-    launch_apply_block(h->dev, h->dev_tiled, mode, nb, x, y, stream, ev);
+    launch_apply_block(h, mode, nb, x, y, stream, ev, work);
     if (ev) {
         pr.n_kernels = 3;
-        pr.names[0] = "k_nn_diag_blk";
-        pr.names[1] = "k_pp_blk";
-        pr.names[2] = "k_pn";
+        static const char *const order[2][3] = {{"k_nn_diag_blk", "k_pp_blk", "k_pn"}, {"k_pn", "k_nn_diag_blk", "k_pp_blk"}};
+        for (int k = 0; k < 3; ++k) pr.names[k] = order[work ? 1 : 0][k];
         pr.calls++;
     }
 }

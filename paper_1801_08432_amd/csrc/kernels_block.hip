@@ -45,7 +45,7 @@ __device__ __forceinline__ Row<T, NB> row_zero() {
 // ------------------------------------------------------------ diagonal + nn
 template <typename T, int RT, int NB>
 __global__ __launch_bounds__(kTS) void k_nn_diag_blk(DevHam P, DevTiled TT, const T *__restrict__ x,
-                                                    T *__restrict__ y) {
+                                                    T *__restrict__ y, const T *__restrict__ slots, int n_slots) {
     typedef Row<T, NB> RowT;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     RowT *Xl = reinterpret_cast<RowT *>(smem_raw);   // Xl[c * RT + r]
@@ -104,7 +104,13 @@ __global__ __launch_bounds__(kTS) void k_nn_diag_blk(DevHam P, DevTiled TT, cons
                     RowT o;
 #pragma unroll
                     for (int v = 0; v < NB; ++v) o.v[v] = acc[r][v];
-                    yb[off + (int64_t)(r0 + r) * nn + c] = o;
+                    const int64_t at = off + (int64_t)(r0 + r) * nn + c;
+                    for (int k = 0; k < n_slots; ++k) {
+                        const RowT t = reinterpret_cast<const RowT *>(slots)[k * P.dim + at];
+#pragma unroll
+                        for (int v = 0; v < NB; ++v) o.v[v] += t.v[v];
+                    }
+                    yb[at] = o;
                 }
         }
     }
@@ -176,20 +182,21 @@ constexpr size_t kLdsMax = 163840;   // LDS per workgroup on gfx950
 // The staged tile of the nn and pp kernels: rt rows (columns) with
 // rt * NB <= kTile, so only these instances exist.
 template <typename T, int NB>
-void launch_nn_blk(int rt, const DevHam &d, const DevTiled &t, const T *x, T *y, size_t lds, hipStream_t st) {
+void launch_nn_blk(int rt, const DevHam &d, const DevTiled &t, const T *x, T *y, const T *slots, int n_slots, size_t lds,
+                   hipStream_t st) {
     if constexpr (4 * NB <= kTile) {
         if (rt == 4) {
-            hipLaunchKernelGGL((k_nn_diag_blk<T, 4, NB>), dim3(t.n_rtiles), dim3(kTS), lds, st, d, t, x, y);
+            hipLaunchKernelGGL((k_nn_diag_blk<T, 4, NB>), dim3(t.n_rtiles), dim3(kTS), lds, st, d, t, x, y, slots, n_slots);
             return;
         }
     }
     if constexpr (2 * NB <= kTile) {
         if (rt == 2) {
-            hipLaunchKernelGGL((k_nn_diag_blk<T, 2, NB>), dim3(t.n_rtiles), dim3(kTS), lds, st, d, t, x, y);
+            hipLaunchKernelGGL((k_nn_diag_blk<T, 2, NB>), dim3(t.n_rtiles), dim3(kTS), lds, st, d, t, x, y, slots, n_slots);
             return;
         }
     }
-    hipLaunchKernelGGL((k_nn_diag_blk<T, 1, NB>), dim3(t.n_rtiles), dim3(kTS), lds, st, d, t, x, y);
+    hipLaunchKernelGGL((k_nn_diag_blk<T, 1, NB>), dim3(t.n_rtiles), dim3(kTS), lds, st, d, t, x, y, slots, n_slots);
 }
 
 template <typename T, int NB>
@@ -211,7 +218,9 @@ void launch_pp_blk(int ct, const DevHam &d, const DevTiled &t, const T *x, T *y,
 }
 
 template <typename T, int NB>
-void launch_block(const DevHam &d, const DevTiled &t, const T *x, T *y, hipStream_t st, void **ev) {
+void launch_block(const fotci_ham *h, const T *x, T *y, hipStream_t st, void **ev, T *slots) {
+    const DevHam &d = h->dev;
+    const DevTiled &t = h->dev_tiled;
     const size_t row = (size_t)NB * sizeof(T);
     // nn: rt rows per pass, pp: ct columns per pass, rt * NB and ct * NB <= kTile
     const int rt = std::min(pick_tile(t.max_nn, (int)row), kTile / NB);
@@ -221,29 +230,42 @@ void launch_block(const DevHam &d, const DevTiled &t, const T *x, T *y, hipStrea
     const size_t lds_pn = (size_t)kPnWaves * kPnTile * kPnRStride * sizeof(T) + (size_t)(t.max_nn + 1) * sizeof(T);
     if (lds_nn > kLdsMax || lds_pp > kLdsMax || lds_pn > kLdsMax)
         fail(FOTCI_EINVAL, "sectors too large for the block kernels' LDS tiles");
-    if (ev) hip_check(hipEventRecord((hipEvent_t)ev[0], st), "event");
-    launch_nn_blk<T, NB>(rt, d, t, x, y, lds_nn, st);
-    if (ev) hip_check(hipEventRecord((hipEvent_t)ev[1], st), "event");
+    int e = 0;
+    auto mark = [&] {
+        if (ev) hip_check(hipEventRecord((hipEvent_t)ev[e++], st), "event");
+    };
+    const int mode = sizeof(T) == 8 ? FOTCI_MODE_F64 : FOTCI_MODE_F32;
+    mark();
+    if (slots) {
+        launch_pn_cores(h, mode, NB, x, slots, st);
+        mark();
+    }
+    launch_nn_blk<T, NB>(rt, d, t, x, y, slots, slots ? h->j->b->p.n : 0, lds_nn, st);
+    mark();
     launch_pp_blk<T, NB>(ct, d, t, x, y, lds_pp, st);
-    if (ev) hip_check(hipEventRecord((hipEvent_t)ev[2], st), "event");
-    launch_pn_block(d, t, sizeof(T) == 8 ? FOTCI_MODE_F64 : FOTCI_MODE_F32, NB, x, y, st);
-    if (ev) hip_check(hipEventRecord((hipEvent_t)ev[3], st), "event");
+    mark();
+    if (!slots) {
+        launch_pn_block(d, t, mode, NB, x, y, st);
+        mark();
+    }
 }
 
 template <typename T>
-void launch_block_nb(const DevHam &d, const DevTiled &t, int nb, const T *x, T *y, hipStream_t st, void **ev) {
+void launch_block_nb(const fotci_ham *h, int nb, const T *x, T *y, hipStream_t st, void **ev, T *slots) {
     switch (nb) {
-        case 2: launch_block<T, 2>(d, t, x, y, st, ev); break;
-        case 4: launch_block<T, 4>(d, t, x, y, st, ev); break;
-        case 8: launch_block<T, 8>(d, t, x, y, st, ev); break;
+        case 2: launch_block<T, 2>(h, x, y, st, ev, slots); break;
+        case 4: launch_block<T, 4>(h, x, y, st, ev, slots); break;
+        case 8: launch_block<T, 8>(h, x, y, st, ev, slots); break;
         default: fail(FOTCI_EINVAL, "n_block must be 1, 2, 4 or 8");
     }
 }
 
 }  // namespace
 
-void launch_apply_block(const DevHam &d, const DevTiled &t, int mode, int nb, const void *x, void *y, void *stream,
-                        void **events) {
+void launch_apply_block(const fotci_ham *h, int mode, int nb, const void *x, void *y, void *stream, void **events,
+                        void *work) {
+    const DevHam &d = h->dev;
+    const DevTiled &t = h->dev_tiled;
     hipStream_t st = (hipStream_t)stream;
     if (mode != FOTCI_MODE_F64 && mode != FOTCI_MODE_F32)
         fail(FOTCI_EINVAL, "block apply_H needs a tiled mode (FOTCI_MODE_F64 or FOTCI_MODE_F32)");
@@ -255,9 +277,9 @@ void launch_apply_block(const DevHam &d, const DevTiled &t, int mode, int nb, co
     // the pn kernel addresses x with 32-bit byte offsets, padding lanes at kOutOfRange
     if (d.dim * nb * es > (int64_t)kOutOfRange) fail(FOTCI_EINVAL, "block too large for 32-bit buffer offsets");
     if (mode == FOTCI_MODE_F64)
-        launch_block_nb<double>(d, t, nb, (const double *)x, (double *)y, st, events);
+        launch_block_nb<double>(h, nb, (const double *)x, (double *)y, st, events, (double *)work);
     else
-        launch_block_nb<float>(d, t, nb, (const float *)x, (float *)y, st, events);
+        launch_block_nb<float>(h, nb, (const float *)x, (float *)y, st, events, (float *)work);
     hip_check(hipGetLastError(), "block apply launch");
 }
 

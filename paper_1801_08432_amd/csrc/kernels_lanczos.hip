@@ -553,7 +553,7 @@ int64_t a256(int64_t x) { return (x + 255) & ~(int64_t)255; }
 // and small arrays.
 struct Layout {
     int64_t ld;   // basis leading dimension (elements): dim rounded up to 64
-    int64_t basis, scratch, y, w, partial, sq, scal, coef, S, ritz, hy, hist, total;   // hist 0: none
+    int64_t basis, scratch, y, w, partial, sq, scal, coef, S, ritz, hy, hist, pn, total;   // hist 0: none; pn -1: none
 };
 
 Layout make_layout(int64_t dim, int es, int nvec, int nscr, int ncoef, int s_cols, int n_keep) {
@@ -589,16 +589,33 @@ Layout make_layout(int64_t dim, int es, int nvec, int nscr, int ncoef, int s_col
     return L;
 }
 
+// Room for the work memory of the recurrence's apply_H (nb vectors) and of the
+// refinement's.
+void add_pn(Layout &L, const fotci_ham *h, int mode, int nb) {
+    const int64_t n = std::max(apply_work_bytes(h, mode, nb),
+                               mode == FOTCI_MODE_F64_PLAIN ? 0 : apply_work_bytes(h, FOTCI_MODE_F64, 1));
+    L.pn = n > 0 ? L.total : -1;
+    L.total = a256(L.total + n);
+}
+
+// Least workspace of a driver: without apply_H's work memory, which a smaller
+// workspace (a card nearly full) does without.
+int64_t least_bytes(const Layout &L) { return L.pn >= 0 ? L.pn : L.total; }
+
 int elem_size(int mode) { return (mode == FOTCI_MODE_F64 || mode == FOTCI_MODE_F64_PLAIN) ? 8 : 4; }
 
 Layout standard_layout(const fotci_ham *h, const fotci_lanczos_opts *o) {
-    return make_layout(h->j->b->dim, elem_size(o->mode), o->n_iter, 0, o->n_iter, o->n_keep, o->n_keep);
+    Layout L = make_layout(h->j->b->dim, elem_size(o->mode), o->n_iter, 0, o->n_iter, o->n_keep, o->n_keep);
+    add_pn(L, h, o->mode, 1);
+    return L;
 }
 
 // Thick restart: n_basis + 1 vectors, n_thick scratch vectors.
 Layout trlan_layout(const fotci_ham *h, const fotci_trlan_opts *o) {
-    return make_layout(h->j->b->dim, elem_size(o->mode), o->n_basis + 1, o->n_thick, o->n_basis + 1,
-                       std::max(o->n_thick, o->n_keep), o->n_keep);
+    Layout L = make_layout(h->j->b->dim, elem_size(o->mode), o->n_basis + 1, o->n_thick, o->n_basis + 1,
+                           std::max(o->n_thick, o->n_keep), o->n_keep);
+    add_pn(L, h, o->mode, 1);
+    return L;
 }
 
 // Block Lanczos: n_iter + 1 row-wise blocks, the block H V_n (mode precision)
@@ -635,6 +652,7 @@ Layout block_layout(const fotci_ham *h, const fotci_block_lanczos_opts *o) {
     L.hy = off;
     off = a256(off + dim * 8);
     L.total = off;
+    add_pn(L, h, o->mode, nb);
     return L;
 }
 
@@ -649,10 +667,15 @@ struct Lz {
     double *w, *partial, *sq, *scal, *coef, *Sd, *ritz, *hy;   // scal: [0] alpha [1] beta [2] norm [3] theta
                                                               // [4] resid [5] norm before reorthogonalisation
     double *hist;   // alpha_i, beta_i of the steps not yet read by the host (null in the block driver)
+    char *pn;       // apply_H work memory, or null
     int reorth;
     int second_passes = 0;
 
-    Lz(const fotci_ham *h_, const Layout &L, int mode_, int reorth_, char *work, double *evecs, hipStream_t st_)
+    // the work memory for a call, null where its mode and block take none
+    void *pn_work(int m, int nb = 1) const { return pn && apply_work_bytes(h, m, nb) > 0 ? pn : nullptr; }
+
+    Lz(const fotci_ham *h_, const Layout &L, int mode_, int reorth_, char *work, int64_t work_bytes, double *evecs,
+       hipStream_t st_)
         : h(h_), st(st_), dim(h_->j->b->dim), ld(L.ld), sb(stream_blocks(dim)), cb(chunk_blocks(dim)),
           mode(mode_), hi_mode(mode_ == FOTCI_MODE_F64_PLAIN ? FOTCI_MODE_F64_PLAIN : FOTCI_MODE_F64),
           reorth(reorth_) {
@@ -668,6 +691,7 @@ struct Lz {
         ritz = evecs ? evecs : (double *)(work + L.ritz);
         hy = (double *)(work + L.hy);
         hist = L.hist ? (double *)(work + L.hist) : nullptr;
+        pn = L.pn >= 0 && work_bytes >= L.total ? work + L.pn : nullptr;
     }
 
     T *vec(int i) const { return basis + (int64_t)i * ld; }
@@ -719,7 +743,7 @@ struct Lz {
 
     void issue(int i, bool three_term, const std::vector<double> &arrow) {
         T *vi = vec(i);
-        launch_apply(h, mode, vi, y, st);
+        launch_apply(h, mode, vi, y, st, pn_work(mode));
         dot_into((const T *)vi, (const T *)y, scal + 0, 0);
         hipLaunchKernelGGL(k_three_term<T>, dim3(sb), dim3(kThreads), 0, st, (const T *)y, (const T *)vi,
                            (const T *)(three_term && i > 0 ? vi - ld : nullptr), (const double *)(scal + 0),
@@ -798,7 +822,7 @@ struct Lz {
             dot_into((const double *)yj, (const double *)yj, scal + 2, 1);
             hipLaunchKernelGGL(k_scale_store<double>, dim3(sb), dim3(kThreads), 0, st, (const double *)yj,
                                (const double *)(scal + 2), yj, dim);
-            launch_apply(h, hi_mode, yj, hy, st);
+            launch_apply(h, hi_mode, yj, hy, st, pn_work(hi_mode));
             if (refine) {
                 dot_into((const double *)yj, (const double *)hy, scal + 3, 0);
             } else {
@@ -818,9 +842,9 @@ struct Lz {
 };
 
 template <typename T>
-void run(const fotci_ham *h, const fotci_lanczos_opts *o, const double *pivot, char *work, double *evals,
+void run(const fotci_ham *h, const fotci_lanczos_opts *o, const double *pivot, char *work, int64_t work_bytes, double *evals,
          double *resid, double *evecs, double *alpha_out, double *beta_out, hipStream_t st) {
-    Lz<T> z(h, standard_layout(h, o), o->mode, o->reorth, work, evecs, st);
+    Lz<T> z(h, standard_layout(h, o), o->mode, o->reorth, work, work_bytes, evecs, st);
     z.start(pivot);
     std::vector<double> al, be, ab;
     const std::vector<double> none;
@@ -877,10 +901,10 @@ void run(const fotci_ham *h, const fotci_lanczos_opts *o, const double *pivot, c
 // s_mu = beta_last L[last, mu] coupling them to v_nt. The first step after a
 // restart subtracts the arrow terms instead of the three-term recurrence.
 template <typename T>
-void run_trlan(const fotci_ham *h, const fotci_trlan_opts *o, const double *pivot, char *work, double *evals,
+void run_trlan(const fotci_ham *h, const fotci_trlan_opts *o, const double *pivot, char *work, int64_t work_bytes, double *evals,
                double *resid, double *evecs, int32_t *stats, hipStream_t st) {
     const Layout L = trlan_layout(h, o);
-    Lz<T> z(h, L, o->mode, o->reorth, work, evecs, st);
+    Lz<T> z(h, L, o->mode, o->reorth, work, work_bytes, evecs, st);
     const int kb = o->n_basis, nt = o->n_thick;
     z.start(pivot);
     std::vector<double> Tm((size_t)(kb + 1) * (kb + 1), 0.0);
@@ -1143,10 +1167,10 @@ double frob(const std::vector<double> &a) {
 }
 
 template <typename T, int NB>
-void run_block(const fotci_ham *h, const fotci_block_lanczos_opts *o, const double *pivot, char *work,
+void run_block(const fotci_ham *h, const fotci_block_lanczos_opts *o, const double *pivot, char *work, int64_t work_bytes,
                double *evals, double *resid, double *evecs, int32_t *n_done, hipStream_t st) {
     constexpr int NQ = NB * NB;
-    Lz<T> z(h, block_layout(h, o), o->mode, FOTCI_REORTH_CGS2, work, evecs, st);
+    Lz<T> z(h, block_layout(h, o), o->mode, FOTCI_REORTH_CGS2, work, work_bytes, evecs, st);
     BlockRun<T, NB> b(z, o->n_iter);
     const int64_t dim = z.dim;
     // V_0 from the pivot block
@@ -1156,7 +1180,7 @@ void run_block(const fotci_ham *h, const fotci_block_lanczos_opts *o, const doub
     double tnorm = 0.0;
     int done = 0, fills = 0;
     for (int n = 0; n < o->n_iter; ++n) {
-        launch_apply_nb(h, z.mode, NB, b.blk(n), z.y, st);
+        launch_apply_nb(h, z.mode, NB, b.blk(n), z.y, st, z.pn_work(z.mode, NB));
         hipLaunchKernelGGL(k_widen<T>, dim3(stream_blocks(dim * NB)), dim3(kThreads), 0, st, (const T *)z.y, z.w,
                            dim * NB);
         b.template multidot<T>(b.blk(n), b.ldb, 1, b.c3 + NQ);   // A_n
@@ -1219,13 +1243,13 @@ void run_block(const fotci_ham *h, const fotci_block_lanczos_opts *o, const doub
 }
 
 template <typename T>
-void run_block_nb(const fotci_ham *h, const fotci_block_lanczos_opts *o, const double *pivot, char *work,
+void run_block_nb(const fotci_ham *h, const fotci_block_lanczos_opts *o, const double *pivot, char *work, int64_t work_bytes,
                   double *evals, double *resid, double *evecs, int32_t *n_done, hipStream_t st) {
     switch (o->n_block) {
-        case 1: run_block<T, 1>(h, o, pivot, work, evals, resid, evecs, n_done, st); break;
-        case 2: run_block<T, 2>(h, o, pivot, work, evals, resid, evecs, n_done, st); break;
-        case 4: run_block<T, 4>(h, o, pivot, work, evals, resid, evecs, n_done, st); break;
-        default: run_block<T, 8>(h, o, pivot, work, evals, resid, evecs, n_done, st); break;
+        case 1: run_block<T, 1>(h, o, pivot, work, work_bytes, evals, resid, evecs, n_done, st); break;
+        case 2: run_block<T, 2>(h, o, pivot, work, work_bytes, evals, resid, evecs, n_done, st); break;
+        case 4: run_block<T, 4>(h, o, pivot, work, work_bytes, evals, resid, evecs, n_done, st); break;
+        default: run_block<T, 8>(h, o, pivot, work, work_bytes, evals, resid, evecs, n_done, st); break;
     }
 }
 
@@ -1238,16 +1262,16 @@ void lanczos_run(const fotci_ham *h, const fotci_lanczos_opts *o, const double *
     if (o->n_keep < 1 || o->n_keep > 16) fail(FOTCI_EINVAL, "n_keep must be in 1..16");
     if (o->n_iter < o->n_keep || o->n_iter > kMaxIter) fail(FOTCI_EINVAL, "n_iter must be in n_keep..4096");
     if (o->reorth != FOTCI_REORTH_CGS2 && o->reorth != FOTCI_REORTH_DGKS) fail(FOTCI_EINVAL, "unknown reorth");
-    if (work_bytes < lanczos_bytes(h, o)) fail(FOTCI_ENOMEM, "Lanczos workspace too small");
+    if (work_bytes < least_bytes(standard_layout(h, o))) fail(FOTCI_ENOMEM, "Lanczos workspace too small");
     if (((uintptr_t)work & 255u) != 0) fail(FOTCI_EINVAL, "workspace must be 256-byte aligned");
     hipStream_t st = (hipStream_t)stream;
     switch (o->mode) {
         case FOTCI_MODE_F64_PLAIN:
         case FOTCI_MODE_F64:
-            run<double>(h, o, pivot, (char *)work, evals, resid, evecs, alpha, beta, st);
+            run<double>(h, o, pivot, (char *)work, work_bytes, evals, resid, evecs, alpha, beta, st);
             break;
         case FOTCI_MODE_F32:
-            run<float>(h, o, pivot, (char *)work, evals, resid, evecs, alpha, beta, st);
+            run<float>(h, o, pivot, (char *)work, work_bytes, evals, resid, evecs, alpha, beta, st);
             break;
         default:
             fail(FOTCI_EINVAL, "unknown mode");
@@ -1274,13 +1298,13 @@ int64_t trlan_bytes(const fotci_ham *h, const fotci_trlan_opts *o) {
 void trlan_run(const fotci_ham *h, const fotci_trlan_opts *o, const double *pivot, void *work, int64_t work_bytes,
                double *evals, double *resid, double *evecs, int32_t *stats, void *stream) {
     check_trlan_opts(o);
-    if (work_bytes < trlan_bytes(h, o)) fail(FOTCI_ENOMEM, "Lanczos workspace too small");
+    if (work_bytes < least_bytes(trlan_layout(h, o))) fail(FOTCI_ENOMEM, "Lanczos workspace too small");
     if (((uintptr_t)work & 255u) != 0) fail(FOTCI_EINVAL, "workspace must be 256-byte aligned");
     hipStream_t st = (hipStream_t)stream;
     if (o->mode == FOTCI_MODE_F32)
-        run_trlan<float>(h, o, pivot, (char *)work, evals, resid, evecs, stats, st);
+        run_trlan<float>(h, o, pivot, (char *)work, work_bytes, evals, resid, evecs, stats, st);
     else
-        run_trlan<double>(h, o, pivot, (char *)work, evals, resid, evecs, stats, st);
+        run_trlan<double>(h, o, pivot, (char *)work, work_bytes, evals, resid, evecs, stats, st);
 }
 
 void check_block_opts(const fotci_block_lanczos_opts *o) {
@@ -1302,14 +1326,14 @@ void block_lanczos_run(const fotci_ham *h, const fotci_block_lanczos_opts *o, co
                        int64_t work_bytes, double *evals, double *resid, double *evecs, int32_t *n_done,
                        void *stream) {
     check_block_opts(o);
-    if (work_bytes < block_lanczos_bytes(h, o)) fail(FOTCI_ENOMEM, "Lanczos workspace too small");
+    if (work_bytes < least_bytes(block_layout(h, o))) fail(FOTCI_ENOMEM, "Lanczos workspace too small");
     if (((uintptr_t)work & 255u) != 0) fail(FOTCI_EINVAL, "workspace must be 256-byte aligned");
     if (((uintptr_t)pivot & 15u) != 0) fail(FOTCI_EINVAL, "pivot block must be 16-byte aligned");
     hipStream_t st = (hipStream_t)stream;
     if (o->mode == FOTCI_MODE_F32)
-        run_block_nb<float>(h, o, pivot, (char *)work, evals, resid, evecs, n_done, st);
+        run_block_nb<float>(h, o, pivot, (char *)work, work_bytes, evals, resid, evecs, n_done, st);
     else
-        run_block_nb<double>(h, o, pivot, (char *)work, evals, resid, evecs, n_done, st);
+        run_block_nb<double>(h, o, pivot, (char *)work, work_bytes, evals, resid, evecs, n_done, st);
 }
 
 }  // namespace fotci

@@ -55,10 +55,26 @@ __global__ __launch_bounds__(kT) void k_ell_values(const int32_t *__restrict__ s
     e32[i] = EllE32{src[i], (float)v};
 }
 
+// sum over the slots of element `at`, four loads in flight
+template <typename T>
+__device__ __forceinline__ T slot_sum(const T *__restrict__ slots, int n, int64_t dim, int64_t at) {
+    T s = 0;
+    int k = 0;
+    for (; k + 4 <= n; k += 4) {
+        const T a = slots[k * dim + at], b = slots[(k + 1) * dim + at], c = slots[(k + 2) * dim + at],
+                d = slots[(k + 3) * dim + at];
+        s += (a + b) + (c + d);
+    }
+    for (; k < n; ++k) s += slots[k * dim + at];
+    return s;
+}
+
 // ------------------------------------------------------------ diagonal + nn
-// RT rows are staged per pass (RT * max_nn * sizeof(T) <= kLdsTile).
+// RT rows are staged per pass (RT * max_nn * sizeof(T) <= kLdsTile). slots:
+// the pn part as n_slots vectors to add, or none.
 template <typename T, int RT>
-__global__ __launch_bounds__(kTS) void k_nn_diag(DevHam P, DevTiled TT, const T *__restrict__ x, T *__restrict__ y) {
+__global__ __launch_bounds__(kTS) void k_nn_diag(DevHam P, DevTiled TT, const T *__restrict__ x, T *__restrict__ y,
+                                                 const T *__restrict__ slots, int n_slots) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     T *Xl = reinterpret_cast<T *>(smem_raw);   // Xl[c * RT + r]
     const int tid = threadIdx.x;
@@ -103,7 +119,10 @@ __global__ __launch_bounds__(kTS) void k_nn_diag(DevHam P, DevTiled TT, const T 
             }
 #pragma unroll
             for (int r = 0; r < RT; ++r)
-                if (r < nr) y[off + (int64_t)(r0 + r) * nn + c] = acc[r];
+                if (r < nr) {
+                    const int64_t at = off + (int64_t)(r0 + r) * nn + c;
+                    y[at] = acc[r] + slot_sum(slots, n_slots, P.dim, at);
+                }
         }
     }
 }
@@ -681,17 +700,29 @@ void launch_pn_nb(const DevHam &d, const DevTiled &t, const T *x, T *y, hipStrea
 }
 
 template <typename T>
-void launch_all(const DevHam &d, const DevTiled &t, const T *x, T *y, hipStream_t st, void **ev) {
-    if (ev) hip_check(hipEventRecord((hipEvent_t)ev[0], st), "event");
+void launch_all(const fotci_ham *h, const T *x, T *y, hipStream_t st, void **ev, T *slots) {
+    const DevHam &d = h->dev;
+    const DevTiled &t = h->dev_tiled;
+    const int mode = sizeof(T) == 8 ? FOTCI_MODE_F64 : FOTCI_MODE_F32;
+    int e = 0;
+    auto mark = [&] {
+        if (ev) hip_check(hipEventRecord((hipEvent_t)ev[e++], st), "event");
+    };
+    mark();
+    const int n_slots = slots ? h->j->b->p.n : 0;
+    if (slots) {
+        launch_pn_cores(h, mode, 1, x, slots, st);
+        mark();
+    }
     const int rt = pick_tile(t.max_nn, sizeof(T));
     const size_t lds_nn = (size_t)rt * t.max_nn * sizeof(T);
     switch (rt) {
-        case 8: hipLaunchKernelGGL((k_nn_diag<T, 8>), dim3(t.n_rtiles), dim3(kTS), lds_nn, st, d, t, x, y); break;
-        case 4: hipLaunchKernelGGL((k_nn_diag<T, 4>), dim3(t.n_rtiles), dim3(kTS), lds_nn, st, d, t, x, y); break;
-        case 2: hipLaunchKernelGGL((k_nn_diag<T, 2>), dim3(t.n_rtiles), dim3(kTS), lds_nn, st, d, t, x, y); break;
-        default: hipLaunchKernelGGL((k_nn_diag<T, 1>), dim3(t.n_rtiles), dim3(kTS), lds_nn, st, d, t, x, y); break;
+        case 8: hipLaunchKernelGGL((k_nn_diag<T, 8>), dim3(t.n_rtiles), dim3(kTS), lds_nn, st, d, t, x, y, slots, n_slots); break;
+        case 4: hipLaunchKernelGGL((k_nn_diag<T, 4>), dim3(t.n_rtiles), dim3(kTS), lds_nn, st, d, t, x, y, slots, n_slots); break;
+        case 2: hipLaunchKernelGGL((k_nn_diag<T, 2>), dim3(t.n_rtiles), dim3(kTS), lds_nn, st, d, t, x, y, slots, n_slots); break;
+        default: hipLaunchKernelGGL((k_nn_diag<T, 1>), dim3(t.n_rtiles), dim3(kTS), lds_nn, st, d, t, x, y, slots, n_slots); break;
     }
-    if (ev) hip_check(hipEventRecord((hipEvent_t)ev[1], st), "event");
+    mark();
     const int ct = pick_tile(t.max_np, sizeof(T));
     const size_t lds_pp = (size_t)ct * t.max_np * sizeof(T);
     const dim3 gpp(pp_grid(t.n_ctiles, kPpRunLines * pp_line_group<T, 1>()));
@@ -710,9 +741,11 @@ void launch_all(const DevHam &d, const DevTiled &t, const T *x, T *y, hipStream_
             default: hipLaunchKernelGGL((k_pp<T, 1, false>), gpp, dim3(kTS), lds_pp, st, d, t, x, y); break;
         }
     }
-    if (ev) hip_check(hipEventRecord((hipEvent_t)ev[2], st), "event");
-    launch_pn_nb<T, 1>(d, t, x, y, st);
-    if (ev) hip_check(hipEventRecord((hipEvent_t)ev[3], st), "event");
+    mark();
+    if (!slots) {
+        launch_pn_nb<T, 1>(d, t, x, y, st);
+        mark();
+    }
 }
 
 }  // namespace
@@ -751,15 +784,14 @@ void launch_pn_block(const DevHam &d, const DevTiled &t, int mode, int nb, const
     }
 }
 
-void launch_apply_tiled(const DevHam &d, const DevTiled &t, int mode, const void *x, void *y, void *stream,
-                        void **events) {
+void launch_apply_tiled(const fotci_ham *h, int mode, const void *x, void *y, void *stream, void **events, void *work) {
     hipStream_t st = (hipStream_t)stream;
-    if (d.p.n_sd == 0) return;
-    if (!t.ok) fail(FOTCI_EINVAL, "basis too large for the tiled kernels (use FOTCI_MODE_F64_PLAIN)");
+    if (h->dev.p.n_sd == 0) return;
+    if (!h->dev_tiled.ok) fail(FOTCI_EINVAL, "basis too large for the tiled kernels (use FOTCI_MODE_F64_PLAIN)");
     if (mode == FOTCI_MODE_F64)
-        launch_all<double>(d, t, (const double *)x, (double *)y, st, events);
+        launch_all<double>(h, (const double *)x, (double *)y, st, events, (double *)work);
     else
-        launch_all<float>(d, t, (const float *)x, (float *)y, st, events);
+        launch_all<float>(h, (const float *)x, (float *)y, st, events, (float *)work);
     hip_check(hipGetLastError(), "apply launch");
 }
 

@@ -32,7 +32,7 @@ EXPORTED = [
     "fotci_lanczos_lowest", "fotci_trlan_workspace_bytes", "fotci_lanczos_thick_restart",
     "fotci_ham_op_counts", "fotci_ham_pn_work", "fotci_ham_set_pn_private_rows",
     "fotci_tridiag_eigh", "fotci_sym_eigh", "fotci_decouple_tbme", "fotci_profile_start",
-    "fotci_profile_stop", "fotci_apply_H_block", "fotci_block_lanczos_workspace_bytes", "fotci_lanczos_block",
+    "fotci_profile_stop", "fotci_apply_H_block", "fotci_apply_work_bytes", "fotci_apply_H_work", "fotci_block_lanczos_workspace_bytes", "fotci_lanczos_block",
 ]
 
 
@@ -108,6 +108,8 @@ def lib():
         "fotci_profile_start": (ctypes.c_int, [P, I32]),
         "fotci_profile_stop": (ctypes.c_int, [P, P, P, P, P]),
         "fotci_apply_H_block": (ctypes.c_int, [P, I32, I32, P, P, P]),
+        "fotci_apply_work_bytes": (I64, [P, I32, I32]),
+        "fotci_apply_H_work": (ctypes.c_int, [P, I32, I32, P, P, P, I64, P]),
         "fotci_block_lanczos_workspace_bytes": (I64, [P, P]),
         "fotci_lanczos_block": (ctypes.c_int, [P, P, P, P, I64, P, P, P, P, P]),
     }
@@ -273,8 +275,26 @@ class Hamiltonian:
             raise ValueError("x must be a contiguous %s device vector of length %d" % (dt, self.dim))
         if y is None:
             y = torch.empty_like(x)
-        _check(lib().fotci_apply_H(self._h, m, _dev_ptr(x), _dev_ptr(y), _stream(stream)))
+        self._apply(m, 1, x, y, stream)
         return y
+
+    def _apply(self, m, n_block, x, y, stream):
+        """fotci_apply_H_work with work memory of this call from torch's allocator, in the stream's order;
+        without it (fewer bytes, other kernels) when the device has none left."""
+        import torch
+        n = lib().fotci_apply_work_bytes(self._h, m, n_block)
+        work = None
+        if n > 0:
+            try:
+                if stream is None:
+                    work = torch.empty(n, dtype=torch.uint8, device=x.device)
+                else:
+                    with torch.cuda.stream(stream):
+                        work = torch.empty(n, dtype=torch.uint8, device=x.device)
+            except torch.cuda.OutOfMemoryError:
+                n = 0
+        _check(lib().fotci_apply_H_work(self._h, m, n_block, _dev_ptr(x), _dev_ptr(y), _dev_ptr(work), max(int(n), 0),
+                                        _stream(stream)))
 
     def apply_block(self, x, y=None, mode="f64", stream=None):
         """Y = H X for a block X of shape (dim, n_block), row-major (vector index fastest)."""
@@ -285,7 +305,7 @@ class Hamiltonian:
             raise ValueError("x must be a contiguous %s device tensor of shape (%d, n_block)" % (dt, self.dim))
         if y is None:
             y = torch.empty_like(x)
-        _check(lib().fotci_apply_H_block(self._h, m, int(x.shape[1]), _dev_ptr(x), _dev_ptr(y), _stream(stream)))
+        self._apply(m, int(x.shape[1]), x, y, stream)
         return y
 
     def vjp(self, x, g, want_dx=True, stream=None, static_scratch=False):
@@ -304,7 +324,11 @@ class Hamiltonian:
                      v_pn=torch.zeros(ns * ns, ns * ns, dtype=torch.float64, device=dev))
         dx = torch.empty_like(x) if want_dx else None
         fn = lib().fotci_apply_H_vjp_static if static_scratch else lib().fotci_apply_H_vjp
-        _check(fn(self._h, _dev_ptr(x), _dev_ptr(g), _dev_ptr(dx), _dev_ptr(grads["eps_p"]),
+        # dx = H g as an apply of its own, which may use work memory
+        split = want_dx and not static_scratch and lib().fotci_apply_work_bytes(self._h, MODE_F64, 1) > 0
+        if split:
+            self._apply(MODE_F64, 1, g, dx, stream)
+        _check(fn(self._h, _dev_ptr(x), _dev_ptr(g), None if split else _dev_ptr(dx), _dev_ptr(grads["eps_p"]),
                   _dev_ptr(grads["eps_n"]), _dev_ptr(grads["v_pp"]), _dev_ptr(grads["v_nn"]),
                   _dev_ptr(grads["v_pn"]), _stream(stream)))
         return dx, grads
@@ -318,6 +342,18 @@ class Hamiltonian:
         _check(lib().fotci_one_body_density(self._h, _dev_ptr(g), _dev_ptr(x), _dev_ptr(rp), _dev_ptr(rn),
                                             _stream(stream)))
         return rp, rn
+
+    def _workspace(self, nbytes, mode, n_block, device):
+        """A driver's workspace of nbytes; without its apply work memory (which the drivers can do without) when
+        the device has not that much left. Returns (tensor, bytes)."""
+        import torch
+        try:
+            return torch.empty(nbytes + 256, dtype=torch.uint8, device=device), nbytes
+        except torch.cuda.OutOfMemoryError:
+            q = lib().fotci_apply_work_bytes
+            part = max(q(self._h, mode, n_block), 0 if mode == MODE_F64_PLAIN else q(self._h, MODE_F64, 1))
+            nbytes -= (part + 255) // 256 * 256
+            return torch.empty(nbytes + 256, dtype=torch.uint8, device=device), nbytes
 
     def lanczos_workspace_bytes(self, n_keep, n_iter, mode="f64", refine=True):
         o = LanczosOpts(n_keep, n_iter, MODES[mode] if isinstance(mode, str) else int(mode), int(refine), 0)
@@ -334,7 +370,7 @@ class Hamiltonian:
         o = LanczosOpts(n_keep, n_iter, m, int(refine), REORTH[reorth])
         nbytes = self.lanczos_workspace_bytes(n_keep, n_iter, m, refine)
         if work is None or work.numel() < nbytes + 256:
-            work = torch.empty(nbytes + 256, dtype=torch.uint8, device=pivot.device)
+            work, nbytes = self._workspace(nbytes, m, 1, pivot.device)
         off = (-work.data_ptr()) % 256
         wptr = ctypes.c_void_p(work.data_ptr() + off)
         if pivot.dtype != torch.float64 or pivot.numel() != self.dim or not pivot.is_contiguous():
@@ -372,7 +408,7 @@ class Hamiltonian:
         o = BlockLanczosOpts(n_keep, nb, n_iter, m, int(refine))
         nbytes = self.block_lanczos_workspace_bytes(n_keep, nb, n_iter, m, refine)
         if work is None or work.numel() < nbytes + 256:
-            work = torch.empty(nbytes + 256, dtype=torch.uint8, device=pivot.device)
+            work, nbytes = self._workspace(nbytes, m, nb, pivot.device)
         wptr = ctypes.c_void_p(work.data_ptr() + (-work.data_ptr()) % 256)
         evals = np.zeros(n_keep)
         resid = np.zeros(n_keep)
@@ -396,7 +432,7 @@ class Hamiltonian:
             _check(int(nbytes))
         if pivot.dtype != torch.float64 or pivot.numel() != self.dim or not pivot.is_contiguous():
             raise ValueError("pivot must be a contiguous float64 device vector of length dim")
-        work = torch.empty(nbytes + 256, dtype=torch.uint8, device=pivot.device)
+        work, nbytes = self._workspace(nbytes, m, 1, pivot.device)
         wptr = ctypes.c_void_p(work.data_ptr() + (-work.data_ptr()) % 256)
         evals = np.zeros(n_keep)
         resid = np.zeros(n_keep)
