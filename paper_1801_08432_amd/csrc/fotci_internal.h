@@ -153,6 +153,7 @@ struct alignas(4) EllE64 {
 // For a proton core u and a pair class the neutron cores that complete the
 // basis quantum numbers are one neutron core group.
 constexpr int kCoreMinShift = 2, kCoreMaxShift = 6;   // byte offset = column << shift: log2(element size * vectors)
+constexpr uint32_t kCoreNoRow = 0xffffffffu;
 constexpr int kCoreMaxPc = 64;      // pair classes
 constexpr int kCoreStates = 8;      // added states of a work item
 constexpr int kCoreMaxPos = 32;     // positions (a state a with up to four states b) of an item in a class
@@ -161,6 +162,7 @@ struct DevCore {
     const uint32_t *u_mask;    // [n_u] proton cores
     const int32_t *u_group;    // [n_u]
     const int32_t *u_row;      // [n_u * ns] proton SD u + a, bit 31: phase of a, -1: none
+    const uint32_t *u_base;    // [n_u * ns] its first element in x, bit 31: phase of a, kCoreNoRow: none
     const int32_t *w_of;       // [u groups * n_pc] neutron core group, -1: none
     const int32_t *w_n;        // [w groups] cores
     const int32_t *w_pad;      // [w groups] cores rounded up to 16
@@ -175,6 +177,7 @@ struct DevCore {
     const int32_t *pair_ab;    // a | b << 8, by a, then b
     const double *v64;         // V[(a b), (c d)] per class
     float *v32;
+    const int32_t *v_tasks;    // tasks of the label densities: {pair class, first, end proton core}
     const int32_t *items;      // work items {proton core, mask of the added states a}
     int32_t n_pc, n_w_code, w_null, n_v, ns;   // w_null: first of a run of null codes as long as the largest group
 };
@@ -244,6 +247,8 @@ struct HostCore {
     std::vector<uint32_t> w_code[kCoreMaxShift - kCoreMinShift + 1];
     std::vector<int32_t> v_src;         // index into v_pn of every element of v
     std::vector<double> v;
+    std::vector<uint32_t> u_base;
+    std::vector<int32_t> v_tasks;       // 3 ints each
     std::vector<int32_t> items;         // 2 ints each
     int item_cols = 0;                  // most row elements of an item
 };
@@ -356,6 +361,9 @@ void fill_core_values(fotci_ham *h);
 int64_t apply_work_bytes(const fotci_ham *h, int mode, int nb);
 // pn part into the slots
 void launch_pn_cores(const fotci_ham *h, int mode, int nb, const void *x, void *slots, void *stream);
+// pn label densities on the cores (added to d_v_pn); false where another kernel
+// is to do it. jumps: the matrix-core jump kernel could.
+bool launch_vjp_cores(const fotci_ham *h, const double *x, const double *g, double *d_v_pn, bool jumps, void *stream);
 void launch_one_body_density(const DevHam &d, const std::vector<int32_t> &h_sec_np, int q0, const double *g,
                              const double *x, double *rho_p, double *rho_n, void *stream);
 // ncol: device buffer of n_nsd doubles for the neutron column sums, or NULL

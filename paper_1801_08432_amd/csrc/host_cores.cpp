@@ -5,6 +5,7 @@
 // pairs (c d) that fill it, one dense matrix V of the pair's (2m, parity)
 // turns them into the pairs (a b), and the results are added to y.
 #include <algorithm>
+#include <array>
 #include <map>
 
 #include "fotci_internal.h"
@@ -14,6 +15,8 @@ namespace fotci {
 namespace {
 
 inline bool odd_below(uint32_t m, int i) { return __builtin_popcount(m & ((1u << i) - 1u)) & 1; }
+
+constexpr int kCoreVjpTasks = 1536;   // three rounds of two workgroups a CU
 
 struct Cores {
     std::vector<uint32_t> mask;              // grouped by (2M, parity), ascending inside a group
@@ -71,11 +74,15 @@ void build_core_tables(fotci_ham *h) {
     };
     const auto pidx = index(b->p), nidx = index(b->n);
     t.u_row.assign(U.mask.size() * (size_t)ns, -1);
+    t.u_base.assign(U.mask.size() * (size_t)ns, kCoreNoRow);
     for (size_t u = 0; u < U.mask.size(); ++u)
         for (int a = 0; a < ns; ++a) {
             if ((U.mask[u] >> a) & 1u) continue;
             const int ip = find(pidx, U.mask[u] | (1u << a));
-            if (ip >= 0) t.u_row[u * ns + a] = ip | (odd_below(U.mask[u], a) ? (int32_t)0x80000000u : 0);
+            if (ip < 0) continue;
+            const uint32_t phase = odd_below(U.mask[u], a) ? 0x80000000u : 0u;
+            t.u_row[u * ns + a] = (int32_t)((uint32_t)ip | phase);
+            t.u_base[u * ns + a] = (uint32_t)b->pstart[ip] | phase;
         }
     // neutron cores: groups, codes
     const int nw = (int)W.count.size();
@@ -188,6 +195,33 @@ void build_core_tables(fotci_ham *h) {
     if (most > kCoreMaxPos) return;
     std::stable_sort(its.begin(), its.end(), [](const It &x, const It &y) { return x.cost > y.cost; });
     for (auto &i : its) t.items.push_back(i.u), t.items.push_back((int32_t)i.amask);
+    // Tasks of the label densities: about equal shares of the work, each of one
+    // class, whose n x n sums a workgroup adds to the result once.
+    std::vector<std::pair<int64_t, std::array<int32_t, 3>>> vt;
+    int64_t all = 0;
+    auto vcost = [&](int u, int p) -> int64_t {
+        const int w = t.w_of[(size_t)U.group[u] * t.n_pc + p], nt = (t.pc_n[p] + 15) / 16;
+        return w < 0 ? 0 : (int64_t)(t.w_pad[w] + 16) * nt * (nt + 2);
+    };
+    const int n_u = (int)U.mask.size();
+    for (int p = 0; p < t.n_pc; ++p)
+        for (int u = 0; u < n_u; ++u) all += vcost(u, p);
+    const int64_t share = std::max<int64_t>(all / kCoreVjpTasks, 4096);
+    for (int p = 0; p < t.n_pc; ++p) {
+        if (t.pc_n[p] > 64) return;
+        int64_t c = 0;
+        int first = 0;
+        for (int u = 0; u < n_u; ++u) {
+            c += vcost(u, p);
+            if (c >= share || (u + 1 == n_u && c > 0)) {
+                vt.push_back({c, {p, first, u + 1}});
+                first = u + 1;
+                c = 0;
+            }
+        }
+    }
+    std::stable_sort(vt.begin(), vt.end(), [](const auto &x, const auto &y) { return x.first > y.first; });
+    for (auto &v : vt) t.v_tasks.insert(t.v_tasks.end(), v.second.begin(), v.second.end());
     t.ok = true;
 }
 

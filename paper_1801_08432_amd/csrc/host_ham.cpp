@@ -536,6 +536,8 @@ std::vector<Item> items(fotci_ham *h) {
     add(hc.pair_ab.data(), hc.pair_ab.size() * 4, &dc.pair_ab);
     add(hc.v.data(), hc.v_src.size() * 8, &dc.v64);
     add(nullptr, hc.v_src.size() * 4, &dc.v32);
+    add(hc.u_base.data(), hc.u_base.size() * 4, &dc.u_base);
+    add(hc.v_tasks.data(), hc.v_tasks.size() * 4, &dc.v_tasks);
     add(hc.items.data(), hc.items.size() * 4, &dc.items);
     for (int sp = 0; sp < 2; ++sp) {
         HostSpeciesTables &t = sp == 0 ? h->tp : h->tn;

@@ -81,3 +81,18 @@ def test_float32_sums_are_reproducible():
     first = ham.apply(x, mode="f32")
     for _ in range(5):
         assert torch.equal(ham.apply(x, mode="f32"), first)
+
+
+@pytest.mark.parametrize("shape", SHAPES + [((1, 3), 3, 3, 0, None)], ids=str)
+def test_label_densities_match_the_oracle(shape):
+    """dV_pn on the cores (and, for the nearly full last shape, on the jump kernel), each entry a sum over the basis of
+    products of O(1) factors in float64: 1e-13 of the norm covers its rounding."""
+    ham, prep, _ = _case(shape)
+    rng = np.random.default_rng(6)
+    x, g = rng.standard_normal(ham.dim), rng.standard_normal(ham.dim)
+    _, grads = ham.vjp(torch.tensor(x, device="cuda"), torch.tensor(g, device="cuda"))
+    ref = fast.densities(prep, g, x)
+    for k in ("v_pn", "v_pp", "v_nn", "eps_p", "eps_n"):
+        r = np.asarray(ref["d_" + k]).ravel()
+        got = grads[k].cpu().numpy().ravel()
+        assert np.linalg.norm(got - r) <= 1e-13 * max(np.linalg.norm(r), 1.0), k
