@@ -264,7 +264,7 @@ int fotci_one_body_density(const fotci_ham *h, const double *g, const double *x,
         for (int q = 0; q < cl.nq; ++q)
             if (cl.delta[q] == 0 && cl.rho[q] == 1) q0 = q;
         if (q0 < 0) fail(FOTCI_EINVAL, "no operator class conserves m and parity");
-        launch_one_body_density(h->dev, h->tc.sec_np, q0, g, x, rho_p, rho_n, stream);
+        launch_one_body_density(h, q0, g, x, rho_p, rho_n, stream);
         return FOTCI_OK;
     });
 }

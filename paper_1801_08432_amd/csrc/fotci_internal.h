@@ -153,6 +153,8 @@ struct alignas(4) EllE64 {
 // For a proton core u and a pair class the neutron cores that complete the
 // basis quantum numbers are one neutron core group.
 constexpr int kCoreMinShift = 2, kCoreMaxShift = 6;   // byte offset = column << shift: log2(element size * vectors)
+constexpr int kObdCores = 32;       // proton cores of a density task
+constexpr int kObdRows = 256;       // proton rows of one
 constexpr uint32_t kCoreNoRow = 0xffffffffu;
 constexpr int kCoreMaxPc = 64;      // pair classes
 constexpr int kCoreStates = 8;      // added states of a work item
@@ -178,6 +180,13 @@ struct DevCore {
     const double *v64;         // V[(a b), (c d)] per class
     float *v32;
     const int32_t *v_tasks;    // tasks of the label densities: {pair class, first, end proton core}
+    // one-body densities: states by (2m, parity), the neutron core group that a
+    // class of states fills up to a basis sector's neutron sector, tasks
+    const int32_t *sp_ptr, *sp_state;
+    const int32_t *ow_of;      // [n_sectors * n_sp], -1: none
+    const int32_t *op_tasks;   // {class, block, first proton core}
+    const int32_t *on_tasks;   // {class, block, basis sector, first core, first row}
+    int32_t n_sp, n_u;
     const int32_t *items;      // work items {proton core, mask of the added states a}
     int32_t n_pc, n_w_code, w_null, n_v, ns;   // w_null: first of a run of null codes as long as the largest group
 };
@@ -249,6 +258,7 @@ struct HostCore {
     std::vector<double> v;
     std::vector<uint32_t> u_base;
     std::vector<int32_t> v_tasks;       // 3 ints each
+    std::vector<int32_t> sp_ptr, sp_state, ow_of, op_tasks, on_tasks;
     std::vector<int32_t> items;         // 2 ints each
     int item_cols = 0;                  // most row elements of an item
 };
@@ -364,8 +374,10 @@ void launch_pn_cores(const fotci_ham *h, int mode, int nb, const void *x, void *
 // pn label densities on the cores (added to d_v_pn); false where another kernel
 // is to do it. jumps: the matrix-core jump kernel could.
 bool launch_vjp_cores(const fotci_ham *h, const double *x, const double *g, double *d_v_pn, bool jumps, void *stream);
-void launch_one_body_density(const DevHam &d, const std::vector<int32_t> &h_sec_np, int q0, const double *g,
-                             const double *x, double *rho_p, double *rho_n, void *stream);
+void launch_one_body_density(const fotci_ham *h, int q0, const double *g, const double *x, double *rho_p,
+                             double *rho_n, void *stream);
+// adds the densities to rho_p and rho_n (null: not wanted); needs hc.ok
+void launch_obd_cores(const fotci_ham *h, const double *g, const double *x, double *rho_p, double *rho_n, void *stream);
 // ncol: device buffer of n_nsd doubles for the neutron column sums, or NULL
 // for the one in the Hamiltonian's workspace
 void launch_vjp(const DevHam &d, const fotci_ham *h, const double *x, const double *g,

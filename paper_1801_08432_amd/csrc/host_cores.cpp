@@ -57,7 +57,9 @@ void build_core_tables(fotci_ham *h) {
     const int ns = h->j->ns;
     HostCore &t = h->hc;
     t = HostCore();
-    if (b->p.n < 1 || b->n.n < 1 || !h->tt.ok) return;
+    // rows and columns that do not exist are read past the end of a vector, at
+    // 2^31 - 2^20 bytes and above
+    if (b->p.n < 1 || b->n.n < 1 || !h->tt.ok || b->dim * 8 > 0x7ff00000) return;
     const Cores U = cores_of(b->p, ms), W = cores_of(b->n, ms);
     t.u_mask = U.mask;
     t.u_group = U.group;
@@ -195,6 +197,37 @@ void build_core_tables(fotci_ham *h) {
     if (most > kCoreMaxPos) return;
     std::stable_sort(its.begin(), its.end(), [](const It &x, const It &y) { return x.cost > y.cost; });
     for (auto &i : its) t.items.push_back(i.u), t.items.push_back((int32_t)i.amask);
+    // One-body densities: states by (2m, parity), a block of 4 x 4 of a class's
+    // entries per task (b block | d block << 4).
+    std::map<std::pair<int, int>, std::vector<int>> sps;
+    for (int a = 0; a < ns; ++a) sps[{ms[a].two_m, ms[a].parity}].push_back(a);
+    const int n_sp = (int)sps.size(), n_s = (int)b->sectors.size();
+    t.sp_ptr.assign(1, 0);
+    t.ow_of.assign((size_t)n_s * n_sp, -1);
+    int cls = 0;
+    for (auto &sp : sps) {
+        for (int a : sp.second) t.sp_state.push_back(a);
+        t.sp_ptr.push_back((int32_t)t.sp_state.size());
+        const int nblk = ((int)sp.second.size() + 3) / 4;
+        for (int s = 0; s < n_s; ++s) {
+            auto it = W.group_of.find({b->two_M - b->sectors[s].two_mp - sp.first.first,
+                                       b->parity * b->sectors[s].parity_p * sp.first.second});
+            if (it != W.group_of.end()) t.ow_of[(size_t)s * n_sp + cls] = it->second;
+        }
+        for (int bb = 0; bb < nblk; ++bb)
+            for (int db = 0; db < nblk; ++db) {
+                const int blk = bb | (db << 4);
+                for (int u = 0; u < (int)U.mask.size(); u += kObdCores) t.op_tasks.insert(t.op_tasks.end(), {cls, blk, u});
+                for (int s = 0; s < n_s; ++s) {
+                    const int w = t.ow_of[(size_t)s * n_sp + cls];
+                    if (w < 0) continue;
+                    for (int j = 0; j < t.w_n[w]; j += 64)
+                        for (int r = 0; r < b->sectors[s].np; r += kObdRows)
+                            t.on_tasks.insert(t.on_tasks.end(), {cls, blk, s, j, r});
+                }
+            }
+        ++cls;
+    }
     // Tasks of the label densities: about equal shares of the work, each of one
     // class, whose n x n sums a workgroup adds to the result once.
     std::vector<std::pair<int64_t, std::array<int32_t, 3>>> vt;

@@ -538,6 +538,13 @@ std::vector<Item> items(fotci_ham *h) {
     add(nullptr, hc.v_src.size() * 4, &dc.v32);
     add(hc.u_base.data(), hc.u_base.size() * 4, &dc.u_base);
     add(hc.v_tasks.data(), hc.v_tasks.size() * 4, &dc.v_tasks);
+    dc.n_sp = (int32_t)hc.sp_ptr.size() - 1;
+    dc.n_u = (int32_t)hc.u_mask.size();
+    add(hc.sp_ptr.data(), hc.sp_ptr.size() * 4, &dc.sp_ptr);
+    add(hc.sp_state.data(), hc.sp_state.size() * 4, &dc.sp_state);
+    add(hc.ow_of.data(), hc.ow_of.size() * 4, &dc.ow_of);
+    add(hc.op_tasks.data(), hc.op_tasks.size() * 4, &dc.op_tasks);
+    add(hc.on_tasks.data(), hc.on_tasks.size() * 4, &dc.on_tasks);
     add(hc.items.data(), hc.items.size() * 4, &dc.items);
     for (int sp = 0; sp < 2; ++sp) {
         HostSpeciesTables &t = sp == 0 ? h->tp : h->tn;

@@ -493,11 +493,11 @@ __global__ __launch_bounds__(kT) void k_obd_proton(DevHam P, int q0, const doubl
 }
 
 // Neutron side: thread = destination neutron SD jn' (a column of its basis
-// sector), block row = a chunk of kObdRows proton rows. Each thread keeps one
+// sector), block row = a chunk of kObdChunk proton rows. Each thread keeps one
 // float64 accumulator per jump into its column (kObdJumps at a time) and
 // walks the rows: g[r, col] is read coalesced across the threads, the x
 // values it pairs with lie in the same row.
-constexpr int kObdRows = 64;
+constexpr int kObdChunk = 64;
 constexpr int kObdJumps = 16;
 
 __global__ __launch_bounds__(kT) void k_obd_neutron(DevHam P, int q0, const double *__restrict__ x,
@@ -507,7 +507,7 @@ __global__ __launch_bounds__(kT) void k_obd_neutron(DevHam P, int q0, const doub
     const int s = P.n_bsector[jn];
     if (s < 0) return;
     const int np = P.sec_np[s], nn = P.sec_nn[s];
-    const int r0 = blockIdx.y * kObdRows, r1 = min(np, r0 + kObdRows);
+    const int r0 = blockIdx.y * kObdChunk, r1 = min(np, r0 + kObdChunk);
     if (r0 >= r1) return;
     const int nq = P.nq;
     const int a0 = P.n.ob_ptr[(int64_t)jn * nq + q0], a1 = P.n.ob_ptr[(int64_t)jn * nq + q0 + 1];
@@ -538,20 +538,23 @@ __global__ __launch_bounds__(kT) void k_obd_neutron(DevHam P, int q0, const doub
 
 }  // namespace
 
-void launch_one_body_density(const DevHam &d, const std::vector<int32_t> &h_sec_np, int q0, const double *g,
-                             const double *x, double *rho_p, double *rho_n, void *stream) {
+void launch_one_body_density(const fotci_ham *h, int q0, const double *g, const double *x, double *rho_p,
+                             double *rho_n, void *stream) {
     hipStream_t st = (hipStream_t)stream;
+    const DevHam &d = h->dev;
     const int n2 = d.ns * d.ns;
-    if (rho_p) {
-        hipLaunchKernelGGL(k_zero, dim3((n2 + kT - 1) / kT), dim3(kT), 0, st, rho_p, n2);
-        hipLaunchKernelGGL(k_obd_proton, dim3(d.p.n_sd), dim3(kT), 0, st, d, q0, x, g, rho_p);
-    }
-    if (rho_n) {
-        hipLaunchKernelGGL(k_zero, dim3((n2 + kT - 1) / kT), dim3(kT), 0, st, rho_n, n2);
-        int max_np = 1;
-        for (int v : h_sec_np) max_np = std::max(max_np, v);
-        const dim3 grid((d.n.n_sd + kT - 1) / kT, (max_np + kObdRows - 1) / kObdRows);
-        hipLaunchKernelGGL(k_obd_neutron, grid, dim3(kT), 0, st, d, q0, x, g, rho_n);
+    for (double *rho : {rho_p, rho_n})
+        if (rho) hipLaunchKernelGGL(k_zero, dim3((n2 + kT - 1) / kT), dim3(kT), 0, st, rho, n2);
+    if (h->hc.ok) {
+        launch_obd_cores(h, g, x, rho_p, rho_n, stream);
+    } else {
+        if (rho_p) hipLaunchKernelGGL(k_obd_proton, dim3(d.p.n_sd), dim3(kT), 0, st, d, q0, x, g, rho_p);
+        if (rho_n) {
+            int max_np = 1;
+            for (int v : h->tc.sec_np) max_np = std::max(max_np, v);
+            const dim3 grid((d.n.n_sd + kT - 1) / kT, (max_np + kObdChunk - 1) / kObdChunk);
+            hipLaunchKernelGGL(k_obd_neutron, grid, dim3(kT), 0, st, d, q0, x, g, rho_n);
+        }
     }
     hip_check(hipGetLastError(), "one-body density launch");
 }

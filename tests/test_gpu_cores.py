@@ -96,3 +96,14 @@ def test_label_densities_match_the_oracle(shape):
         r = np.asarray(ref["d_" + k]).ravel()
         got = grads[k].cpu().numpy().ravel()
         assert np.linalg.norm(got - r) <= 1e-13 * max(np.linalg.norm(r), 1.0), k
+
+
+@pytest.mark.parametrize("shape", SHAPES + [((1, 3), 3, 3, 0, None), ((1, 3, 5), 6, 5, 1, None)], ids=str)
+def test_one_body_densities_match_the_oracle(shape):
+    """The last shape has groups of more than one block of columns; five states of one m take two blocks of entries."""
+    ham, prep, _ = _case(shape)
+    rng = np.random.default_rng(7)
+    x, g = rng.standard_normal(ham.dim), rng.standard_normal(ham.dim)
+    rp, rn = ham.one_body_density(torch.tensor(g, device="cuda"), torch.tensor(x, device="cuda"))
+    for got, ref in zip((rp, rn), fast.one_body_densities(prep, g, x)):
+        assert np.linalg.norm(got.cpu().numpy() - ref) <= 1e-13 * max(np.linalg.norm(ref), 1.0)
