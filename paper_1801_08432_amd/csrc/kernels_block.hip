@@ -85,6 +85,16 @@ __global__ __launch_bounds__(kTS) void k_nn_diag_blk(DevHam P, DevTiled TT, cons
 #pragma unroll
                 for (int v = 0; v < NB; ++v) acc[r][v] = (dp[r] + dnc) * xr.v[v];
             }
+            // the pn part's slots, all rows of one in flight together
+#pragma unroll 2
+            for (int k = 0; k < n_slots; ++k)
+#pragma unroll
+                for (int r = 0; r < RT; ++r) {
+                    const RowT t = reinterpret_cast<const RowT *>(slots)[k * P.dim + off +
+                                                                         (int64_t)(r0 + min(r, nr - 1)) * nn + c];
+#pragma unroll
+                    for (int v = 0; v < NB; ++v) acc[r][v] += t.v[v];
+                }
 #pragma unroll 8
             for (int e = 0; e < E; ++e) {
                 const auto ent = ell_load(ev, eb + (int64_t)e * nn + c);
@@ -104,13 +114,7 @@ __global__ __launch_bounds__(kTS) void k_nn_diag_blk(DevHam P, DevTiled TT, cons
                     RowT o;
 #pragma unroll
                     for (int v = 0; v < NB; ++v) o.v[v] = acc[r][v];
-                    const int64_t at = off + (int64_t)(r0 + r) * nn + c;
-                    for (int k = 0; k < n_slots; ++k) {
-                        const RowT t = reinterpret_cast<const RowT *>(slots)[k * P.dim + at];
-#pragma unroll
-                        for (int v = 0; v < NB; ++v) o.v[v] += t.v[v];
-                    }
-                    yb[at] = o;
+                    yb[off + (int64_t)(r0 + r) * nn + c] = o;
                 }
         }
     }

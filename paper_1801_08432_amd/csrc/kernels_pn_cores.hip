@@ -11,10 +11,12 @@
 // times, and the dense matrices cover the pairs of a class (1.8 to 2.4 times the
 // useful multiply-adds in 20 states) instead of the labels of an operator class
 // (6.2 times). pn part at 5p5n in 20 states, dim 18.6 M: float32 2.84 -> 1.64 ms,
-// float64 6.90 -> 2.39 ms (4p4n: 0.377 -> 0.186 and 0.662 -> 0.265 ms). What bounds it now is the
-// vector cache: a load of 64 gathered elements touches about 18 64-byte pieces
-// (32 in float64), since columns that hold a given state d lie about four apart,
-// and the cache's tag look-ups are 70% busy; matrix cores 31%.
+// float64 6.90 -> 2.39 ms (4p4n: 0.377 -> 0.186 and 0.662 -> 0.265 ms). What bounds it (float32,
+// with parts taken out): 0.25 ms to set up and write out the items, one
+// workgroup per CU, 0.3 ms to load the operands of the tasks, and subtiles that
+// issue 41% of the time to the vector and 31% to the matrix units; without the
+// loads of x and its codes it still runs at 1.49 ms, without the matrix
+// instructions at 1.35 ms.
 #include <cmath>
 
 #include "tiled_common.h"
@@ -105,7 +107,8 @@ __device__ __forceinline__ void core_pass(const CoreLds &S, const uint32_t *kl, 
     }
     T xa[KST], xb[KST];
     auto loadc = [&](uint32_t (&c)[KST], int sub) {
-        const unsigned o = 64u * (unsigned)min(sub, s1 - 1);
+        // up to two subtiles past the last: other codes of the table, whose x is not used
+        const unsigned o = 64u * (unsigned)sub;
 #pragma unroll
         for (int k = 0; k < KST; ++k) c[k] = buffer_load_u32(cr, co[k] + o);
     };
