@@ -30,6 +30,9 @@ constexpr int kLazySteps = 16;
 constexpr int kRowsPerThread = 8;
 constexpr int kChunk = kThreads * kRowsPerThread;   // rows per block in the tall-skinny kernels
 constexpr int kMaxIter = 4096;
+constexpr int kFewBlocks = 64;       // one lane per block of a coefficient's parts
+constexpr int kFewVectors = 8;
+constexpr int kDeferBlocks = 1024;   // 8 KiB of norm parts, read by every block of k_norm_store
 
 __device__ __forceinline__ double wave_sum(double v) {
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
@@ -70,12 +73,28 @@ __global__ __launch_bounds__(kThreads) void k_finish(const double *__restrict__ 
     if (threadIdx.x == 0) out[0] = take_sqrt ? sqrt(acc) : acc;
 }
 
-// w = y - alpha v_i - beta v_{i-1} (beta term skipped when vprev is null)
+// Sum of nb partial sums, in k_finish's order, for every thread of a block: the
+// kernel that needs the sum takes it itself, which saves a launch (a few
+// microseconds each, half of a step's time at dimensions near 1e5).
+__device__ __forceinline__ double block_total(const double *__restrict__ partial, int nb, double *lds) {
+    double acc = 0.0;
+    for (int i = threadIdx.x; i < nb; i += kThreads) acc += partial[i];
+    acc = block_sum(acc, lds);
+    if (threadIdx.x == 0) lds[0] = acc;
+    __syncthreads();
+    return lds[0];
+}
+
+// w = y - alpha v_i - beta v_{i-1} (beta term skipped when vprev is null);
+// alpha is the sum of the nb partial sums of <v_i, y>, left in *alpha
 template <typename T>
 __global__ __launch_bounds__(kThreads) void k_three_term(const T *__restrict__ y, const T *__restrict__ vi,
-                                                         const T *__restrict__ vprev, const double *alpha,
-                                                         const double *beta, double *__restrict__ w, int64_t n) {
-    const double a = *alpha;
+                                                         const T *__restrict__ vprev, const double *__restrict__ partial,
+                                                         int nb, double *alpha, const double *beta,
+                                                         double *__restrict__ w, int64_t n) {
+    __shared__ double lds[kWaves];
+    const double a = block_total(partial, nb, lds);
+    if (blockIdx.x == 0 && threadIdx.x == 0) *alpha = a;
     const double b = vprev ? *beta : 0.0;
     for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += (int64_t)gridDim.x * kThreads) {
         double t = (double)y[i] - a * (double)vi[i];
@@ -217,6 +236,13 @@ __global__ __launch_bounds__(kThreads) void k_multidot(const T *__restrict__ V, 
                                                        const double *__restrict__ w, int64_t n,
                                                        double *__restrict__ partial, double *__restrict__ sq_partial) {
     __shared__ double lds[kWaves][256];
+    if (gridDim.y > 1) {   // a share of kFewVectors basis vectors per block
+        const int j0 = blockIdx.y * kFewVectors;
+        V += (int64_t)j0 * ld;
+        partial += (int64_t)j0 * gridDim.x;
+        k = min(k - j0, kFewVectors);
+        if (blockIdx.y > 0) sq_partial = nullptr;
+    }
     if ((int64_t)(blockIdx.x + 1) * kChunk <= n)
         multidot_body<T, true>(V, ld, k, w, n, partial, sq_partial, lds);
     else
@@ -297,6 +323,58 @@ __global__ __launch_bounds__(kThreads) void k_subtract(const T *__restrict__ V, 
         subtract_body<T, true>(V, ld, k, cs, w, n, sq_partial, cs + k);
     else
         subtract_body<T, false>(V, ld, k, cs, w, n, sq_partial, cs + k);
+}
+
+// The subtraction for few rows: a thread per row and kFewVectors loads of the
+// basis in flight. With eight rows a thread a vector of 93,710 rows fills 46
+// blocks, which then walk the basis at the latency of its loads. c: the nb <= 64
+// partial sums of every coefficient (k_multidot's), which each block adds up
+// itself, a wave per coefficient.
+template <typename T>
+__global__ __launch_bounds__(kThreads) void k_subtract_few(const T *__restrict__ V, int64_t ld, int k,
+                                                           const double *__restrict__ c, int nb, double *__restrict__ w,
+                                                           int64_t n, double *__restrict__ sq_partial) {
+    extern __shared__ double cs[];   // k coefficients, then kWaves reduction slots
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+#pragma unroll 4
+    for (int j = wid; j < k; j += kWaves) {
+        const double v = wave_sum(lane < nb ? c[(int64_t)j * nb + lane] : 0.0);
+        if (lane == 0) cs[j] = v;
+    }
+    __syncthreads();
+    const int64_t r = (int64_t)blockIdx.x * kThreads + threadIdx.x, at = r < n ? r : n - 1;
+    double acc = 0.0;
+    int j = 0;
+    for (; j + kFewVectors <= k; j += kFewVectors) {
+        T v[kFewVectors];
+#pragma unroll
+        for (int u = 0; u < kFewVectors; ++u) v[u] = V[(int64_t)(j + u) * ld + at];
+#pragma unroll
+        for (int u = 0; u < kFewVectors; ++u) acc += cs[j + u] * (double)v[u];
+    }
+    for (; j < k; ++j) acc += cs[j] * (double)V[(int64_t)j * ld + at];
+    const double t = w[at] - acc;
+    if (r < n) w[r] = t;
+    const double sq = block_sum(r < n ? t * t : 0.0, cs + k);
+    if (threadIdx.x == 0) sq_partial[blockIdx.x] = sq;
+}
+
+// out = (T)(in / beta) with beta = sqrt of the sum of nb partial sums, left in
+// ab[1]; ab = {alpha, beta} is also copied to hist
+template <typename T>
+__global__ __launch_bounds__(kThreads) void k_norm_store(const double *__restrict__ in, const double *__restrict__ partial,
+                                                         int nb, double *ab, double *hist, T *__restrict__ out,
+                                                         int64_t n) {
+    __shared__ double lds[kWaves];
+    const double beta = sqrt(block_total(partial, nb, lds));
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        ab[1] = beta;
+        hist[0] = ab[0];
+        hist[1] = beta;
+    }
+    const double s = 1.0 / beta;
+    for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += (int64_t)gridDim.x * kThreads)
+        out[i] = (T)(in[i] * s);
 }
 
 // out = (T)(in * scale) with scale = 1 / *denom
@@ -553,7 +631,7 @@ int64_t a256(int64_t x) { return (x + 255) & ~(int64_t)255; }
 // and small arrays.
 struct Layout {
     int64_t ld;   // basis leading dimension (elements): dim rounded up to 64
-    int64_t basis, scratch, y, w, partial, sq, scal, coef, S, ritz, hy, hist, pn, total;   // hist 0: none; pn -1: none
+    int64_t basis, scratch, y, w, partial, sq, wsq, scal, coef, S, ritz, hy, hist, pn, total;   // hist 0: none; pn -1: none
 };
 
 Layout make_layout(int64_t dim, int es, int nvec, int nscr, int ncoef, int s_cols, int n_keep) {
@@ -572,6 +650,8 @@ Layout make_layout(int64_t dim, int es, int nvec, int nscr, int ncoef, int s_col
     L.partial = off;
     off = a256(off + (int64_t)std::max(ncoef, 1) * nb * 8);
     L.sq = off;
+    off = a256(off + nb * 8);
+    L.wsq = off;
     off = a256(off + nb * 8);
     L.scal = off;
     off = a256(off + 64 * 8);
@@ -667,6 +747,9 @@ struct Lz {
     double *w, *partial, *sq, *scal, *coef, *Sd, *ritz, *hy;   // scal: [0] alpha [1] beta [2] norm [3] theta
                                                               // [4] resid [5] norm before reorthogonalisation
     double *hist;   // alpha_i, beta_i of the steps not yet read by the host (null in the block driver)
+    double *wsq;    // block sums of w^2 after a subtraction
+    int n_wsq = 0;
+    bool deferred = false;   // beta_i is still to be taken from wsq
     char *pn;       // apply_H work memory, or null
     int reorth;
     int second_passes = 0;
@@ -690,6 +773,7 @@ struct Lz {
         Sd = (double *)(work + L.S);
         ritz = evecs ? evecs : (double *)(work + L.ritz);
         hy = (double *)(work + L.hy);
+        wsq = (double *)(work + L.wsq);
         hist = L.hist ? (double *)(work + L.hist) : nullptr;
         pn = L.pn >= 0 && work_bytes >= L.total ? work + L.pn : nullptr;
     }
@@ -728,9 +812,12 @@ struct Lz {
     // The next vector is w / beta computed on the device, so the host only has
     // to look at beta to stop at an invariant subspace, which it can do late:
     // steps after a breakdown work on garbage that is then discarded.
-    void step_async(int i, bool three_term, const std::vector<double> &arrow) {
-        issue(i, three_term, arrow);
-        hip_check(hipMemcpyAsync(hist + 2 * i, scal, 16, hipMemcpyDeviceToDevice, st), "lanczos copy");
+    // read: the host reads hist before store_next(i); otherwise, with few blocks,
+    // beta and the copy are left to store_next.
+    void step_async(int i, bool three_term, const std::vector<double> &arrow, bool read) {
+        const bool defer = !read && cb <= kDeferBlocks;
+        issue(i, three_term, arrow, defer);
+        if (!defer) hip_check(hipMemcpyAsync(hist + 2 * i, scal, 16, hipMemcpyDeviceToDevice, st), "lanczos copy");
     }
 
     // alpha, beta of steps i0 <= i < i1 (issued with step_async) to the host
@@ -741,12 +828,13 @@ struct Lz {
         hip_check(hipStreamSynchronize(st), "lanczos sync");
     }
 
-    void issue(int i, bool three_term, const std::vector<double> &arrow) {
+    void issue(int i, bool three_term, const std::vector<double> &arrow, bool defer = false) {
         T *vi = vec(i);
         launch_apply(h, mode, vi, y, st, pn_work(mode));
-        dot_into((const T *)vi, (const T *)y, scal + 0, 0);
+        hipLaunchKernelGGL((k_dot_partial<T, T>), dim3(sb), dim3(kThreads), 0, st, (const T *)vi, (const T *)y, dim,
+                           partial);
         hipLaunchKernelGGL(k_three_term<T>, dim3(sb), dim3(kThreads), 0, st, (const T *)y, (const T *)vi,
-                           (const T *)(three_term && i > 0 ? vi - ld : nullptr), (const double *)(scal + 0),
+                           (const T *)(three_term && i > 0 ? vi - ld : nullptr), (const double *)partial, sb, scal + 0,
                            (const double *)(scal + 1), w, dim);
         if (!arrow.empty()) {
             const int na = (int)arrow.size();
@@ -754,17 +842,31 @@ struct Lz {
             hipLaunchKernelGGL(k_subtract<T>, dim3(cb), dim3(kThreads), (size_t)(na + kWaves) * 8, st,
                                (const T *)basis, ld, na, (const double *)coef, w, dim, (double *)nullptr);
         }
-        // pass 1 (with DGKS also ||w|| before it); the subtract leaves ||w||^2 block sums in partial
-        auto pass = [&](bool norm_before) {
-            hipLaunchKernelGGL(k_multidot<T>, dim3(cb), dim3(kThreads), 0, st, (const T *)basis, ld, i + 1,
-                               (const double *)w, dim, partial, norm_before ? sq : (double *)nullptr);
-            hipLaunchKernelGGL(k_reduce_rows, dim3(i + 1), dim3(kThreads), 0, st, (const double *)partial, cb, coef);
-            hipLaunchKernelGGL(k_subtract<T>, dim3(cb), dim3(kThreads), (size_t)(i + 1 + kWaves) * 8, st,
-                               (const T *)basis, ld, i + 1, (const double *)coef, w, dim, partial);
-            hipLaunchKernelGGL(k_finish, dim3(1), dim3(kThreads), 0, st, (const double *)partial, cb, scal + 1, 1);
-        };
+        // Few blocks of rows (dimensions to 1.3e5): the basis is split over blocks
+        // too, and the subtraction takes a row per thread and adds up the
+        // coefficients' parts itself (a float64 step at 93,710, 25 vectors in the
+        // mean: 139 -> 115 us; float32 179 -> 110). The norm after pass 1 is only for DGKS.
         const bool dgks = reorth == FOTCI_REORTH_DGKS;
-        pass(dgks);
+        const bool few = cb <= kFewBlocks;
+        n_wsq = few ? (int)((dim + kThreads - 1) / kThreads) : cb;
+        // pass 1 (with DGKS also ||w|| before it); the subtract leaves ||w||^2 block sums in wsq
+        auto pass = [&](bool norm_before, bool norm_after) {
+            const dim3 grid(cb, few ? (unsigned)(i + kFewVectors) / kFewVectors : 1u);
+            hipLaunchKernelGGL(k_multidot<T>, grid, dim3(kThreads), 0, st, (const T *)basis, ld, i + 1,
+                               (const double *)w, dim, partial, norm_before ? sq : (double *)nullptr);
+            const size_t lds = (size_t)(i + 1 + kWaves) * 8;
+            if (few) {
+                hipLaunchKernelGGL(k_subtract_few<T>, dim3(n_wsq), dim3(kThreads), lds, st, (const T *)basis, ld, i + 1,
+                                   (const double *)partial, cb, w, dim, wsq);
+            } else {
+                hipLaunchKernelGGL(k_reduce_rows, dim3(i + 1), dim3(kThreads), 0, st, (const double *)partial, cb, coef);
+                hipLaunchKernelGGL(k_subtract<T>, dim3(cb), dim3(kThreads), lds, st, (const T *)basis, ld, i + 1,
+                                   (const double *)coef, w, dim, wsq);
+            }
+            if (norm_after)
+                hipLaunchKernelGGL(k_finish, dim3(1), dim3(kThreads), 0, st, (const double *)wsq, n_wsq, scal + 1, 1);
+        };
+        pass(dgks, dgks);
         bool second = true;
         if (dgks) {
             hipLaunchKernelGGL(k_finish, dim3(1), dim3(kThreads), 0, st, (const double *)sq, cb, scal + 5, 1);
@@ -775,14 +877,20 @@ struct Lz {
             second = nn[0] < 0.7071067811865476 * nn[1];
         }
         if (second) {
-            pass(false);
+            pass(false, !defer);
             ++second_passes;
         }
+        deferred = defer;
         hip_check(hipGetLastError(), "lanczos launch");
     }
 
     // v_{i+1} = w / beta (beta in scal[1] from the last step)
     void store_next(int i) {
+        if (deferred) {
+            hipLaunchKernelGGL(k_norm_store<T>, dim3(sb), dim3(kThreads), 0, st, (const double *)w, (const double *)wsq, n_wsq,
+                               scal, hist + 2 * i, vec(i + 1), dim);
+            return;
+        }
         hipLaunchKernelGGL(k_scale_store<T>, dim3(sb), dim3(kThreads), 0, st, (const double *)w,
                            (const double *)(scal + 1), vec(i + 1), dim);
     }
@@ -865,8 +973,9 @@ void run(const fotci_ham *h, const fotci_lanczos_opts *o, const double *pivot, c
     for (int i = 0; i < o->n_iter; ++i) {
         bool go = true;
         if (lazy) {
-            z.step_async(i, true, none);
-            if (i == o->n_iter - 1 || (i + 1) % kLazySteps == 0) {
+            const bool read = i == o->n_iter - 1 || (i + 1) % kLazySteps == 0;
+            z.step_async(i, true, none, read);
+            if (read) {
                 z.collect(collected, i + 1, ab);
                 for (int j = collected; j <= i && go; ++j)
                     go = accept(j, ab[2 * (j - collected)], ab[2 * (j - collected) + 1]);
@@ -935,8 +1044,9 @@ void run_trlan(const fotci_ham *h, const fotci_trlan_opts *o, const double *pivo
             bool go = true;
             ++applies;
             if (lazy) {
-                z.step_async(i, i > j0 || j0 == 0, i == j0 ? arrow : std::vector<double>());
-                if (i == kb - 1 || (i + 1 - j0) % kLazySteps == 0) {
+                const bool read = i == kb - 1 || (i + 1 - j0) % kLazySteps == 0;
+                z.step_async(i, i > j0 || j0 == 0, i == j0 ? arrow : std::vector<double>(), read);
+                if (read) {
                     z.collect(collected, i + 1, ab);
                     for (int j = collected; j <= i && go; ++j)
                         go = accept(j, ab[2 * (j - collected)], ab[2 * (j - collected) + 1]);
