@@ -365,6 +365,38 @@ void fill_species_values(fotci_ham *h) {
 
 namespace {
 
+// Whether an n x n matrix is finite, exactly symmetric and zero between rows
+// of different class (the id of their 2M and parity): in blocks, so that the
+// mirrored half is read along its rows too. A training step checks 160,000 pn elements; one at a time, each with its
+// four states taken apart, they took 1.2 of the 1.6 ms of fotci_ham_set_values.
+bool clean(const double *v, const std::vector<int> &cls) {
+    const size_t n = cls.size();
+    constexpr size_t B = 32;
+    for (size_t r0 = 0; r0 < n; r0 += B)
+        for (size_t c0 = r0; c0 < n; c0 += B) {
+            const size_t r1 = std::min(n, r0 + B), c1 = std::min(n, c0 + B);
+            bool bad = false;
+            for (size_t r = r0; r < r1; ++r)
+                for (size_t c = c0; c < c1; ++c) {
+                    const double x = v[r * n + c];
+                    // x - x is 0 for finite x only
+                    bad |= (x != v[c * n + r]) | (x - x != 0.0) | ((x != 0.0) & (cls[r] != cls[c]));
+                }
+            if (bad) return false;
+        }
+    return true;
+}
+
+// Ids of the (2M, parity) of all pairs a < b, or of all (a, b).
+std::vector<int> pair_classes(const std::vector<MState> &ms, bool ordered) {
+    std::map<std::pair<int, int>, int> ids;
+    std::vector<int> out;
+    for (size_t a = 0; a < ms.size(); ++a)
+        for (size_t b = ordered ? a + 1 : 0; b < ms.size(); ++b)
+            out.push_back(ids.insert({{ms[a].two_m + ms[b].two_m, ms[a].parity * ms[b].parity}, (int)ids.size()}).first->second);
+    return out;
+}
+
 void validate(const fotci_jumps *j, const double *spe_p, const double *spe_n, const double *v_pp,
               const double *v_nn, const double *v_pn) {
     if (!spe_p || !spe_n || !v_pp || !v_nn || !v_pn) fail(FOTCI_EINVAL, "interaction array is NULL");
@@ -378,6 +410,11 @@ void validate(const fotci_jumps *j, const double *spe_p, const double *spe_n, co
         }
     for (int o = 0; o < j->b->n_orbits; ++o)
         if (!std::isfinite(spe_p[o]) || !std::isfinite(spe_n[o])) fail(FOTCI_EINVAL, "non-finite energy");
+    {
+        const std::vector<int> like = pair_classes(ms, true), pn = pair_classes(ms, false);
+        if (clean(v_pp, like) && clean(v_nn, like) && clean(v_pn, pn)) return;
+    }
+    // the loops below name the first fault
     for (const double *v : {v_pp, v_nn}) {
         for (int r = 0; r < np; ++r)
             for (int c = 0; c < np; ++c) {
