@@ -191,6 +191,20 @@ struct DevCore {
     int32_t n_pc, n_w_code, w_null, n_v, ns;   // w_null: first of a run of null codes as long as the largest group
 };
 
+// Tables of the proton two-body densities: SDs t with two protons taken out,
+// like-particle pair classes (a < b of one (2m, parity)).
+constexpr int kPairsMost = 48;      // pairs of a class
+constexpr int kPairsTasks = 1024;
+struct DevPairs {
+    const uint32_t *t_base;    // [n_t * n_pairs] first element of row t + a + b, bit 31: phase, kCoreNoRow: none
+    const int32_t *t_nn;       // [n_t * n_pc] columns of the rows of t with a pair of the class
+    const int32_t *pc_first;   // [n_pc + 1]
+    const int32_t *pc_pair;    // pairs by class
+    const int32_t *cls_of;     // class of every entry of pc_pair
+    const int32_t *tasks;      // {class, first, end t}
+    int32_t n_pc;
+};
+
 // Code of "no column" for byte shift s: shifted, it lies past any vector
 // (2 GiB) and a row's byte offset added to it does not wrap.
 constexpr uint32_t core_null(int shift) { return 0x80000000u >> shift; }
@@ -293,6 +307,12 @@ struct HostTiled {
     bool ok = false;
 };
 
+struct HostPairs {
+    std::vector<uint32_t> t_base;
+    std::vector<int32_t> t_nn, pc_first, pc_pair, cls_of, tasks;   // tasks empty: not used for this basis
+    int n_pc = 0;
+};
+
 // Host-side tables (built once per jumps + interaction layout).
 struct HostCommonTables {
     std::vector<int32_t> p_sector, n_local, sec_nn, sec_nfirst, sec_pfirst, sec_np, conjq;
@@ -319,6 +339,8 @@ struct fotci_ham {
     fotci::HostTiled tt;
     fotci::HostCore hc;
     fotci::DevCore dev_core{};
+    fotci::HostPairs hp;
+    fotci::DevPairs dev_pairs{};
     fotci::DevTiled dev_tiled{};
     int32_t pn_priv = 1;                  // see fotci_ham_set_pn_private_rows
     // device
@@ -365,6 +387,9 @@ void build_tiled_tables(fotci_ham *h);
 // tables of the core kernels (host_cores.cpp); fill: the matrix elements only
 void build_core_tables(fotci_ham *h);
 void fill_core_values(fotci_ham *h);
+void build_pair_tables(fotci_ham *h);
+// proton two-body densities, diagonal labels among them; false where the sampled products are to do them
+bool launch_vjp_pairs(const fotci_ham *h, const double *x, const double *g, double *d_v_pp, void *stream);
 // Bytes of work with which apply_H (nb vectors row-wise) runs its pn part on
 // the core kernels, 0 where it does not use them: one slot of dim * nb elements
 // per proton.

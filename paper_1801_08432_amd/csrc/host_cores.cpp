@@ -258,6 +258,86 @@ void build_core_tables(fotci_ham *h) {
     t.ok = true;
 }
 
+void build_pair_tables(fotci_ham *h) {
+    const fotci_basis *b = h->j->b;
+    const auto &ms = b->ms;
+    const int ns = h->j->ns, npairs = h->j->npairs;
+    HostPairs &t = h->hp;
+    t = HostPairs();
+    if (b->p.n < 2 || !h->tt.ok || b->dim * 8 > 0x7ff00000) return;
+    std::map<std::pair<int, int>, std::vector<std::pair<int, int>>> cls;
+    for (int a = 0; a < ns; ++a)
+        for (int c = a + 1; c < ns; ++c) cls[{ms[a].two_m + ms[c].two_m, ms[a].parity * ms[c].parity}].push_back({a, c});
+    std::vector<std::pair<int, int>> st;   // the states of every entry of pc_pair
+    t.pc_first.assign(1, 0);
+    for (auto &c : cls) {
+        if ((int)c.second.size() > kPairsMost) return;
+        for (auto &p : c.second) {
+            t.pc_pair.push_back(pair_index(p.first, p.second, ns));
+            t.cls_of.push_back(t.n_pc);
+            st.push_back(p);
+        }
+        t.pc_first.push_back((int32_t)t.pc_pair.size());
+        ++t.n_pc;
+    }
+    std::vector<uint32_t> ts;
+    std::vector<std::pair<uint32_t, int32_t>> idx;
+    for (size_t i = 0; i < b->p.sd.size(); ++i) {
+        const uint32_t m = b->p.sd[i];
+        idx.push_back({m, (int32_t)i});
+        for (uint32_t r = m; r; r &= r - 1)
+            for (uint32_t q = r & (r - 1); q; q &= q - 1) ts.push_back(m & ~(r & (0u - r)) & ~(q & (0u - q)));
+    }
+    std::sort(ts.begin(), ts.end());
+    ts.erase(std::unique(ts.begin(), ts.end()), ts.end());
+    std::sort(idx.begin(), idx.end());
+    // Multiply-adds of the two forms (the sampled product's in tiles of 32): all
+    // densities before and after at shares of 0.35 to 0.88: 8.5 / 7.1 ms (20 states, 5p5n,
+    // 0.35), 0.73 / 0.61 (4p4n, 0.54), 4.3 / 4.0 (3p6n, 0.77), 8.1 / 5.9 (18 states, 8p4n, 0.79),
+    // 19.0 / 18.7 (5p8n, 0.88). The table stays below 64 MiB.
+    int64_t dense = 0, mine = 0;
+    for (auto &s : b->sectors) dense += (int64_t)((s.np + 31) / 32 * 32) * ((s.np + 31) / 32 * 32) * s.nn;
+    if ((int64_t)ts.size() * npairs * 4 > ((int64_t)64 << 20)) return;
+    const int n_t = (int)ts.size();
+    std::vector<uint32_t> base((size_t)n_t * npairs, kCoreNoRow);
+    std::vector<int32_t> nn((size_t)n_t * t.n_pc, 0);
+    for (int i = 0; i < n_t; ++i)
+        for (size_t e = 0; e < st.size(); ++e) {
+            const uint32_t add = (1u << st[e].first) | (1u << st[e].second);
+            if (ts[i] & add) continue;
+            auto it = std::lower_bound(idx.begin(), idx.end(), std::make_pair(ts[i] | add, (int32_t)0));
+            if (it == idx.end() || it->first != (ts[i] | add)) continue;
+            const bool odd = odd_below(ts[i], st[e].first) != odd_below(ts[i], st[e].second);
+            base[(size_t)i * npairs + t.pc_pair[e]] = (uint32_t)b->pstart[it->second] | (odd ? 0x80000000u : 0u);
+            nn[(size_t)i * t.n_pc + t.cls_of[e]] = b->sectors[b->p_basis_sector[it->second]].nn;
+        }
+    auto cost = [&](int i, int c) -> int64_t {
+        const int nt = (t.pc_first[c + 1] - t.pc_first[c] + 15) / 16;
+        return (int64_t)nn[(size_t)i * t.n_pc + c] * 256 * nt * nt;
+    };
+    for (int c = 0; c < t.n_pc; ++c)
+        for (int i = 0; i < n_t; ++i) mine += cost(i, c);
+    if (mine > dense) return;
+    std::vector<std::pair<int64_t, std::array<int32_t, 3>>> vt;
+    const int64_t share = std::max<int64_t>(mine / kPairsTasks, 1 << 16);
+    for (int c = 0; c < t.n_pc; ++c) {
+        int64_t sum = 0;
+        int first = 0;
+        for (int i = 0; i < n_t; ++i) {
+            sum += cost(i, c);
+            if (sum >= share || (i + 1 == n_t && sum > 0)) {
+                vt.push_back({sum, {c, first, i + 1}});
+                first = i + 1;
+                sum = 0;
+            }
+        }
+    }
+    std::stable_sort(vt.begin(), vt.end(), [](const auto &x, const auto &y) { return x.first > y.first; });
+    for (auto &v : vt) t.tasks.insert(t.tasks.end(), v.second.begin(), v.second.end());
+    t.t_base = std::move(base);
+    t.t_nn = std::move(nn);
+}
+
 void fill_core_values(fotci_ham *h) {
     HostCore &t = h->hc;
     t.v.resize(t.v_src.size());

@@ -573,6 +573,15 @@ std::vector<Item> items(fotci_ham *h) {
     add(hc.pair_ab.data(), hc.pair_ab.size() * 4, &dc.pair_ab);
     add(hc.v.data(), hc.v_src.size() * 8, &dc.v64);
     add(nullptr, hc.v_src.size() * 4, &dc.v32);
+    HostPairs &hp = h->hp;
+    DevPairs &dp = h->dev_pairs;
+    dp.n_pc = hp.n_pc;
+    add(hp.t_base.data(), hp.t_base.size() * 4, &dp.t_base);
+    add(hp.t_nn.data(), hp.t_nn.size() * 4, &dp.t_nn);
+    add(hp.pc_first.data(), hp.pc_first.size() * 4, &dp.pc_first);
+    add(hp.pc_pair.data(), hp.pc_pair.size() * 4, &dp.pc_pair);
+    add(hp.cls_of.data(), hp.cls_of.size() * 4, &dp.cls_of);
+    add(hp.tasks.data(), hp.tasks.size() * 4, &dp.tasks);
     add(hc.u_base.data(), hc.u_base.size() * 4, &dc.u_base);
     add(hc.v_tasks.data(), hc.v_tasks.size() * 4, &dc.v_tasks);
     dc.n_sp = (int32_t)hc.sp_ptr.size() - 1;
@@ -641,6 +650,7 @@ extern "C" int fotci_set_interaction_impl(const fotci_jumps *j, const double *sp
         build_species_tables(j, 1, h->tn);
         build_tiled_tables(h);
         build_core_tables(h);
+        build_pair_tables(h);
         fill_species_values(h);
         fill_dev_scalars(h);
         int64_t off = 0;

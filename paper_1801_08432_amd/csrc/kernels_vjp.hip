@@ -613,7 +613,6 @@ void launch_vjp(const DevHam &d, const fotci_ham *h, const double *x, const doub
         }
         return tiles;
     };
-    const bool sd_p = d_v_pp && tt.ok, sd_n = d_v_nn && tt.ok;
     double *dcol = nullptr;
     const bool need_n = d_spe_n || d_v_nn;
     if (need_n) {
@@ -622,9 +621,11 @@ void launch_vjp(const DevHam &d, const fotci_ham *h, const double *x, const doub
         dcol = ncol ? ncol : d.scratch_ncol;
         hipLaunchKernelGGL(k_zero, dim3((d.n.n_sd + kT - 1) / kT), dim3(kT), 0, st, dcol, d.n.n_sd);
     }
-    if (d_spe_p || d_v_pp)
+    const bool pairs = d_v_pp && launch_vjp_pairs(h, x, g, d_v_pp, stream);   // every pp label
+    const bool sd_p = d_v_pp && tt.ok && !pairs, sd_n = d_v_nn && tt.ok;
+    if (d_spe_p || (d_v_pp && !pairs))
         hipLaunchKernelGGL(k_diag_rows, dim3((d.p.n_sd + kDiagRows - 1) / kDiagRows), dim3(kT), 0, st, d, x, g, d_spe_p,
-                           d_v_pp);
+                           pairs ? (double *)nullptr : d_v_pp);
     if (need_n) {
         int max_np = 1;
         for (int v : h->tc.sec_np) max_np = std::max(max_np, v);
@@ -633,7 +634,7 @@ void launch_vjp(const DevHam &d, const fotci_ham *h, const double *x, const doub
                            dcol);
         hipLaunchKernelGGL(k_diag_neutron, dim3(cols), dim3(kT), 0, st, d, (const double *)dcol, d_spe_n, d_v_nn);
     }
-    if (d_v_pp && !sd_p) hipLaunchKernelGGL(k_vjp_off<false>, dim3(d.p.n_sd), dim3(kT), 0, st, d, x, g, d_v_pp);
+    if (d_v_pp && !pairs && !sd_p) hipLaunchKernelGGL(k_vjp_off<false>, dim3(d.p.n_sd), dim3(kT), 0, st, d, x, g, d_v_pp);
     if (d_v_nn && !sd_n) hipLaunchKernelGGL(k_vjp_off<true>, dim3(d.n.n_sd), dim3(kT), 0, st, d, x, g, d_v_nn);
     if (sd_p) {
         const int64_t tiles = sddmm_tiles(false);
