@@ -163,8 +163,8 @@ constexpr int kCoreRowElems = 14336;   // row elements of a work item in LDS (fl
 struct DevCore {
     const uint32_t *u_mask;    // [n_u] proton cores
     const int32_t *u_group;    // [n_u]
-    const int32_t *u_row;      // [n_u * ns] proton SD u + a, bit 31: phase of a, -1: none
-    const uint32_t *u_base;    // [n_u * ns] its first element in x, bit 31: phase of a, kCoreNoRow: none
+    const uint32_t *u_base;    // [n_u * ns] first element of row u + a in x, bit 31: phase of a, kCoreNoRow: none
+    const int32_t *u_nn;       // [n_u * ns] its columns
     const int32_t *w_of;       // [u groups * n_pc] neutron core group, -1: none
     const int32_t *w_n;        // [w groups] cores
     const int32_t *w_pad;      // [w groups] cores rounded up to 16
@@ -266,7 +266,7 @@ struct HostCore {
     bool ok = false;
     int n_pc = 0, w_null = 0;
     std::vector<uint32_t> u_mask;
-    std::vector<int32_t> u_group, u_row, w_of, w_n, w_pad, w_off, pc_n, pc_pair, pc_v, pc_first, pair_ab;
+    std::vector<int32_t> u_group, u_nn, w_of, w_n, w_pad, w_off, pc_n, pc_pair, pc_v, pc_first, pair_ab;
     std::vector<uint32_t> w_code[kCoreMaxShift - kCoreMinShift + 1];
     std::vector<int32_t> v_src;         // index into v_pn of every element of v
     std::vector<double> v;

@@ -75,7 +75,7 @@ void build_core_tables(fotci_ham *h) {
         return it != v.end() && it->first == m ? it->second : -1;
     };
     const auto pidx = index(b->p), nidx = index(b->n);
-    t.u_row.assign(U.mask.size() * (size_t)ns, -1);
+    t.u_nn.assign(U.mask.size() * (size_t)ns, 0);
     t.u_base.assign(U.mask.size() * (size_t)ns, kCoreNoRow);
     for (size_t u = 0; u < U.mask.size(); ++u)
         for (int a = 0; a < ns; ++a) {
@@ -83,7 +83,7 @@ void build_core_tables(fotci_ham *h) {
             const int ip = find(pidx, U.mask[u] | (1u << a));
             if (ip < 0) continue;
             const uint32_t phase = odd_below(U.mask[u], a) ? 0x80000000u : 0u;
-            t.u_row[u * ns + a] = (int32_t)((uint32_t)ip | phase);
+            t.u_nn[u * ns + a] = b->sectors[b->p_basis_sector[ip]].nn;
             t.u_base[u * ns + a] = (uint32_t)b->pstart[ip] | phase;
         }
     // neutron cores: groups, codes
@@ -157,9 +157,8 @@ void build_core_tables(fotci_ham *h) {
         std::vector<std::pair<int, int>> st;   // (state, row columns)
         int64_t all = 0;
         for (int a = 0; a < ns; ++a) {
-            const int32_t row = t.u_row[(size_t)u * ns + a];
-            if (row == -1) continue;
-            st.push_back({a, b->sectors[b->p_basis_sector[row & 0x7fffffff]].nn});
+            if (t.u_base[(size_t)u * ns + a] == kCoreNoRow) continue;
+            st.push_back({a, t.u_nn[(size_t)u * ns + a]});
             all += st.back().second;
         }
         // as few items as fit, of about equal size

@@ -559,7 +559,7 @@ std::vector<Item> items(fotci_ham *h) {
     dc.n_v = (int32_t)hc.v_src.size();
     add(hc.u_mask.data(), hc.u_mask.size() * 4, &dc.u_mask);
     add(hc.u_group.data(), hc.u_group.size() * 4, &dc.u_group);
-    add(hc.u_row.data(), hc.u_row.size() * 4, &dc.u_row);
+    add(hc.u_nn.data(), hc.u_nn.size() * 4, &dc.u_nn);
     add(hc.w_of.data(), hc.w_of.size() * 4, &dc.w_of);
     add(hc.w_n.data(), hc.w_n.size() * 4, &dc.w_n);
     add(hc.w_pad.data(), hc.w_pad.size() * 4, &dc.w_pad);

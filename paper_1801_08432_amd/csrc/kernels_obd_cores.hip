@@ -71,7 +71,7 @@ __global__ __launch_bounds__(kOcThreads) void k_obd_p(DevHam P, DevCore C, const
         for (int i = 0; i < 4; ++i) {
             rb[i] = b[i] < 0 ? kCoreNoRow : C.u_base[(int64_t)u * C.ns + b[i]];
             rd[i] = d[i] < 0 ? kCoreNoRow : C.u_base[(int64_t)u * C.ns + d[i]];
-            if (rb[i] != kCoreNoRow) nn = P.sec_nn[P.p_sector[C.u_row[(int64_t)u * C.ns + b[i]] & 0x7fffffff]];
+            if (rb[i] != kCoreNoRow) nn = C.u_nn[(int64_t)u * C.ns + b[i]];
         }
         // the phases of u + a are the core's: the sign goes onto the loaded value
         unsigned ob[4], od[4];

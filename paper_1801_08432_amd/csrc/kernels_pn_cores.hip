@@ -56,7 +56,7 @@ struct CoreLds {
 // sum of a row element's few addends is exact, so their order does not matter.
 template <typename T, int KST>
 __device__ __forceinline__ void core_pass(const CoreLds &S, const uint32_t *kl, const uint32_t *ml, int nk, int nm, int n,
-                                          unsigned pv, const int32_t *__restrict__ pab, unsigned wbytes, int wpad, int s0,
+                                          unsigned pv, const int32_t *pab, unsigned wbytes, int wpad, int s0,
                                           int s1, unsigned null_off, int shift, __amdgpu_buffer_rsrc_t xr,
                                           __amdgpu_buffer_rsrc_t cr, __amdgpu_buffer_rsrc_t dr,
                                           __amdgpu_buffer_rsrc_t vr, int lane, unsigned own) {
@@ -190,8 +190,8 @@ __global__ __launch_bounds__(core_threads<T>()) void k_pn_core(DevHam P, DevCore
                                                           int n_items, int lognb, int ycols, const T *__restrict__ x,
                                                           T *__restrict__ slots) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
-    __shared__ uint32_t s_xo[32], s_ps[32];
-    __shared__ int32_t s_row[32], s_yo[32], s_nn[32];
+    __shared__ uint32_t s_xo[32], s_ps[32], s_base[32];
+    __shared__ int32_t s_yo[32], s_nn[32], s_pp[kCoreMaxPc];
     __shared__ int s_task[kCoreMaxPc + 1], s_w[kCoreMaxPc];
     __shared__ int s_nk[kCoreMaxPc], s_np[kCoreMaxPc], s_next;
     const int NT = blockDim.x;
@@ -213,6 +213,12 @@ __global__ __launch_bounds__(core_threads<T>()) void k_pn_core(DevHam P, DevCore
     S.yl = reinterpret_cast<double *>(smem_raw);
     uint32_t *kl = reinterpret_cast<uint32_t *>(S.yl + ycols + NT);   // [ns * ns]
     uint32_t *ml = kl + ns * ns;                                      // [npc * kCoreMaxPos]
+    // the pair tables, so that the lists below are built without a load
+    int32_t *s_pair = reinterpret_cast<int32_t *>(ml + npc * kCoreMaxPos);   // [ns * ns]
+    int32_t *s_first = s_pair + ns * ns;                                     // [npc * (ns + 1)]
+    for (int i = tid; i < ns * ns; i += NT) s_pair[i] = C.pair_ab[i];
+    for (int i = tid; i < npc * (ns + 1); i += NT) s_first[i] = C.pc_first[i];
+    for (int i = tid; i < npc; i += NT) s_pp[i] = C.pc_pair[i];
     S.kl = kl;
     S.ml = ml;
     S.xo = s_xo;
@@ -220,10 +226,9 @@ __global__ __launch_bounds__(core_threads<T>()) void k_pn_core(DevHam P, DevCore
     S.yo = s_yo;
     if (wid == 0) {
         const int a = lane & 31;
-        const int32_t row = a < ns ? C.u_row[(int64_t)u * ns + a] : -1;
-        const int ip = row == -1 ? 0 : row & 0x7fffffff;
-        const int rn = P.sec_nn[P.p_sector[ip]];
-        const unsigned xo = (((unsigned)P.p_pstart[ip] << lognb) + g0) << es;
+        const uint32_t rb = a < ns ? C.u_base[(int64_t)u * ns + a] : kCoreNoRow;
+        const int rn = a < ns ? C.u_nn[(int64_t)u * ns + a] : 0;
+        const unsigned xo = (((rb & 0x7fffffffu) << lognb) + g0) << es;
         // rows of the item's states, one after another
         const int mine = (amask >> a) & 1u ? rn : 0;
         int nn = mine;
@@ -232,9 +237,9 @@ __global__ __launch_bounds__(core_threads<T>()) void k_pn_core(DevHam P, DevCore
             if (a >= o) nn += v;
         }
         if (lane < 32) {
-            s_row[a] = row;
-            s_ps[a] = (uint32_t)row & 0x80000000u;
-            s_xo[a] = row == -1 ? kOutOfRange : xo;
+            s_base[a] = rb;
+            s_ps[a] = rb & 0x80000000u;
+            s_xo[a] = rb == kCoreNoRow ? kOutOfRange : xo;
             s_nn[a] = rn;
             s_yo[a] = nn - mine;
         }
@@ -267,12 +272,12 @@ __global__ __launch_bounds__(core_threads<T>()) void k_pn_core(DevHam P, DevCore
     const uint64_t below = (1ull << lane) - 1ull;
     for (int pc = wid; pc < npc; pc += NT / 64) {
         if (s_w[pc] < 0) continue;   // uniform per wave
-        const int n = C.pc_n[pc], pp = C.pc_pair[pc];
+        const int pp = s_pp[pc], n = s_first[pc * (ns + 1) + ns];
         int nk = 0;
         for (int p = lane; p - lane < n; p += 64) {
-            const int ab = C.pair_ab[pp + min(p, n - 1)];
+            const int ab = s_pair[pp + min(p, n - 1)];
             const int c = ab & 255;
-            const bool ok = p < n && s_row[c] != -1;
+            const bool ok = p < n && s_base[c] != kCoreNoRow;
             const uint64_t km = __ballot(ok);
             if (ok) kl[pp + nk + __popcll(km & below)] = (uint32_t)c | ((uint32_t)(ab >> 8) << 5) | ((uint32_t)p << 10);
             nk += __popcll(km);
@@ -280,8 +285,8 @@ __global__ __launch_bounds__(core_threads<T>()) void k_pn_core(DevHam P, DevCore
         // positions: every state a of the item with four of its states b at a time
         int f0 = 0, nba = 0;
         if (lane < ns && ((amask >> lane) & 1u)) {
-            f0 = C.pc_first[pc * (ns + 1) + lane];
-            nba = C.pc_first[pc * (ns + 1) + lane + 1] - f0;
+            f0 = s_first[pc * (ns + 1) + lane];
+            nba = s_first[pc * (ns + 1) + lane + 1] - f0;
         }
         int np = 0;
         for (int lev = 0;; ++lev) {
@@ -322,10 +327,11 @@ __global__ __launch_bounds__(core_threads<T>()) void k_pn_core(DevHam P, DevCore
         const int w = __builtin_amdgcn_readfirstlane(s_w[pc]);
         const int nk = __builtin_amdgcn_readfirstlane(s_nk[pc]), np = __builtin_amdgcn_readfirstlane(s_np[pc]);
         const int s0 = (task - __builtin_amdgcn_readfirstlane(s_task[pc])) * kCoreSub;
-        const int wpad = C.w_pad[w], n = C.pc_n[pc], pp = C.pc_pair[pc];
+        const int pp = __builtin_amdgcn_readfirstlane(s_pp[pc]);
+        const int wpad = C.w_pad[w], n = C.pc_n[pc];
         const unsigned wbytes = (unsigned)C.w_off[w] * 4u, pv = (unsigned)C.pc_v[pc];
         const int s1 = min(s0 + kCoreSub, wpad >> 4);
-        const int32_t *pab = C.pair_ab + pp;
+        const int32_t *pab = s_pair + pp;
         for (int m0 = 0; m0 < np; m0 += kCorePos)
             for (int k0 = 0; k0 < nk; k0 += kCoreSlots) {
                 const int nm = min(np - m0, kCorePos), kk = min(nk - k0, kCoreSlots);
@@ -352,7 +358,7 @@ __global__ __launch_bounds__(core_threads<T>()) void k_pn_core(DevHam P, DevCore
     const uint32_t um = C.u_mask[u];
     for (uint32_t m = amask; m; m &= m - 1) {
         const int a = __builtin_ctz(m);
-        const int64_t base = P.p_pstart[s_row[a] & 0x7fffffff];
+        const int64_t base = s_base[a] & 0x7fffffffu;
         const int k = __builtin_popcount(um & ((1u << a) - 1u));
         T *out = slots + (((int64_t)k * P.dim + base) << lognb) + g0;
         const int nn = s_nn[a], o = s_yo[a];
@@ -368,7 +374,7 @@ void launch_cores(const fotci_ham *h, int nb, const T *x, T *slots, hipStream_t 
     const unsigned grid = nb == 1 ? (unsigned)n : (unsigned)((n + 7) / 8 * 8 * nb);
     const int ns = h->j->ns;
     auto bytes = [&](int threads) {
-        return ((size_t)hc.item_cols + threads) * 8 + ((size_t)ns * ns + (size_t)hc.n_pc * kCoreMaxPos) * 4;
+        return ((size_t)hc.item_cols + threads) * 8 + ((size_t)2 * ns * ns + (size_t)hc.n_pc * (kCoreMaxPos + ns + 1)) * 4;
     };
     // Workgroups of four waves where their rows leave room for as many of them
     // as the registers do (three float32, two float64), else one of all the
