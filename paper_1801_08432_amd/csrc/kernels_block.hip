@@ -85,7 +85,12 @@ __global__ __launch_bounds__(kTS) void k_nn_diag_blk(DevHam P, DevTiled TT, cons
 #pragma unroll
                 for (int v = 0; v < NB; ++v) acc[r][v] = (dp[r] + dnc) * xr.v[v];
             }
-            // the pn part's slots, all rows of one in flight together
+            // the pn part's slots, all rows of one in flight together, in a sum of their own
+            T sl[RT][NB];
+#pragma unroll
+            for (int r = 0; r < RT; ++r)
+#pragma unroll
+                for (int v = 0; v < NB; ++v) sl[r][v] = 0;
 #pragma unroll 2
             for (int k = 0; k < n_slots; ++k)
 #pragma unroll
@@ -93,7 +98,7 @@ __global__ __launch_bounds__(kTS) void k_nn_diag_blk(DevHam P, DevTiled TT, cons
                     const RowT t = reinterpret_cast<const RowT *>(slots)[k * P.dim + off +
                                                                          (int64_t)(r0 + min(r, nr - 1)) * nn + c];
 #pragma unroll
-                    for (int v = 0; v < NB; ++v) acc[r][v] += t.v[v];
+                    for (int v = 0; v < NB; ++v) sl[r][v] += t.v[v];
                 }
 #pragma unroll 8
             for (int e = 0; e < E; ++e) {
@@ -113,7 +118,7 @@ __global__ __launch_bounds__(kTS) void k_nn_diag_blk(DevHam P, DevTiled TT, cons
                 if (r < nr) {
                     RowT o;
 #pragma unroll
-                    for (int v = 0; v < NB; ++v) o.v[v] = acc[r][v];
+                    for (int v = 0; v < NB; ++v) o.v[v] = acc[r][v] + sl[r][v];
                     yb[off + (int64_t)(r0 + r) * nn + c] = o;
                 }
         }

@@ -58,7 +58,7 @@ __global__ __launch_bounds__(kT) void k_ell_values(const int32_t *__restrict__ s
 // ------------------------------------------------------------ diagonal + nn
 // RT rows are staged per pass (RT * max_nn * sizeof(T) <= kLdsTile). slots:
 // the pn part as n_slots vectors to add, or none.
-template <typename T, int RT>
+template <typename T, int RT, bool SLOTS>
 __global__ __launch_bounds__(kTS) void k_nn_diag(DevHam P, DevTiled TT, const T *__restrict__ x, T *__restrict__ y,
                                                  const T *__restrict__ slots, int n_slots) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -92,17 +92,21 @@ __global__ __launch_bounds__(kTS) void k_nn_diag(DevHam P, DevTiled TT, const T 
             T acc[RT];
             const T dnc = dn[nf + c];
 #pragma unroll
-            for (int r = 0; r < RT; ++r) acc[r] = 0;
-            // the slots of all rows before the walk, 2 RT loads in flight: the kernel
-            // at pf 5p5n takes 0.29 ms with five slots, 0.20 without (0.34 when each
-            // row's were summed as it was written; 4p4n in float64 0.0605 / 0.0565)
+            for (int r = 0; r < RT; ++r) acc[r] = (dp[r] + dnc) * Xl[c * RT + (r ^ slab_swz<T, RT>(c))];
+            // the slots of all rows before the walk, 2 RT loads in flight, and a sum of
+            // their own until the end (the walk's small terms keep their digits): the kernel at pf 5p5n
+            // takes 0.28 ms with five slots, 0.20 without (0.34 when each row's
+            // were summed as it was written; float64 0.62, 0.49 and 0.68 ms)
+            T sl[RT];
+            if constexpr (SLOTS) {
+#pragma unroll
+                for (int r = 0; r < RT; ++r) sl[r] = 0;
 #pragma unroll 2
-            for (int k = 0; k < n_slots; ++k)
+                for (int k = 0; k < n_slots; ++k)
 #pragma unroll
-                for (int r = 0; r < RT; ++r)
-                    acc[r] += slots[k * P.dim + off + (int64_t)(r0 + min(r, nr - 1)) * nn + c];
-#pragma unroll
-            for (int r = 0; r < RT; ++r) acc[r] += (dp[r] + dnc) * Xl[c * RT + (r ^ slab_swz<T, RT>(c))];
+                    for (int r = 0; r < RT; ++r)
+                        sl[r] += __builtin_nontemporal_load(slots + k * P.dim + off + (int64_t)(r0 + min(r, nr - 1)) * nn + c);
+            }
 #pragma unroll 8
             for (int e = 0; e < E; ++e) {
                 const auto ent = ell_load(ev, eb + (int64_t)e * nn + c);
@@ -116,8 +120,9 @@ __global__ __launch_bounds__(kTS) void k_nn_diag(DevHam P, DevTiled TT, const T 
 #pragma unroll
             for (int r = 0; r < RT; ++r)
                 if (r < nr) {
-                    const int64_t at = off + (int64_t)(r0 + r) * nn + c;
-                    y[at] = acc[r];
+                    T v = acc[r];
+                    if constexpr (SLOTS) v += sl[r];
+                    y[off + (int64_t)(r0 + r) * nn + c] = v;
                 }
         }
     }
@@ -695,6 +700,18 @@ void launch_pn_nb(const DevHam &d, const DevTiled &t, const T *x, T *y, hipStrea
                            x, y);
 }
 
+template <typename T, bool SLOTS>
+void launch_nn(int rt, const DevHam &d, const DevTiled &t, const T *x, T *y, const T *slots, int n, hipStream_t st) {
+    const size_t lds = (size_t)rt * t.max_nn * sizeof(T);
+    const dim3 grid(t.n_rtiles), block(kTS);
+    switch (rt) {
+        case 8: hipLaunchKernelGGL((k_nn_diag<T, 8, SLOTS>), grid, block, lds, st, d, t, x, y, slots, n); break;
+        case 4: hipLaunchKernelGGL((k_nn_diag<T, 4, SLOTS>), grid, block, lds, st, d, t, x, y, slots, n); break;
+        case 2: hipLaunchKernelGGL((k_nn_diag<T, 2, SLOTS>), grid, block, lds, st, d, t, x, y, slots, n); break;
+        default: hipLaunchKernelGGL((k_nn_diag<T, 1, SLOTS>), grid, block, lds, st, d, t, x, y, slots, n); break;
+    }
+}
+
 template <typename T>
 void launch_all(const fotci_ham *h, const T *x, T *y, hipStream_t st, void **ev, T *slots) {
     const DevHam &d = h->dev;
@@ -711,13 +728,10 @@ void launch_all(const fotci_ham *h, const T *x, T *y, hipStream_t st, void **ev,
         mark();
     }
     const int rt = pick_tile(t.max_nn, sizeof(T));
-    const size_t lds_nn = (size_t)rt * t.max_nn * sizeof(T);
-    switch (rt) {
-        case 8: hipLaunchKernelGGL((k_nn_diag<T, 8>), dim3(t.n_rtiles), dim3(kTS), lds_nn, st, d, t, x, y, slots, n_slots); break;
-        case 4: hipLaunchKernelGGL((k_nn_diag<T, 4>), dim3(t.n_rtiles), dim3(kTS), lds_nn, st, d, t, x, y, slots, n_slots); break;
-        case 2: hipLaunchKernelGGL((k_nn_diag<T, 2>), dim3(t.n_rtiles), dim3(kTS), lds_nn, st, d, t, x, y, slots, n_slots); break;
-        default: hipLaunchKernelGGL((k_nn_diag<T, 1>), dim3(t.n_rtiles), dim3(kTS), lds_nn, st, d, t, x, y, slots, n_slots); break;
-    }
+    if (slots)
+        launch_nn<T, true>(rt, d, t, x, y, slots, n_slots, st);
+    else
+        launch_nn<T, false>(rt, d, t, x, y, slots, 0, st);
     mark();
     const int ct = pick_tile(t.max_np, sizeof(T));
     const size_t lds_pp = (size_t)ct * t.max_np * sizeof(T);
