@@ -298,18 +298,18 @@ void build_pair_tables(fotci_ham *h) {
     for (auto &s : b->sectors) dense += (int64_t)((s.np + 31) / 32 * 32) * ((s.np + 31) / 32 * 32) * s.nn;
     if ((int64_t)ts.size() * npairs * 4 > ((int64_t)64 << 20)) return;
     const int n_t = (int)ts.size();
-    std::vector<uint32_t> base((size_t)n_t * npairs, kCoreNoRow);
+    std::map<std::pair<int, int>, int> cols;   // columns of the rows of a proton (2M, parity)
+    for (auto &s : b->sectors) cols[{s.two_mp, s.parity_p}] = s.nn;
     std::vector<int32_t> nn((size_t)n_t * t.n_pc, 0);
-    for (int i = 0; i < n_t; ++i)
-        for (size_t e = 0; e < st.size(); ++e) {
-            const uint32_t add = (1u << st[e].first) | (1u << st[e].second);
-            if (ts[i] & add) continue;
-            auto it = std::lower_bound(idx.begin(), idx.end(), std::make_pair(ts[i] | add, (int32_t)0));
-            if (it == idx.end() || it->first != (ts[i] | add)) continue;
-            const bool odd = odd_below(ts[i], st[e].first) != odd_below(ts[i], st[e].second);
-            base[(size_t)i * npairs + t.pc_pair[e]] = (uint32_t)b->pstart[it->second] | (odd ? 0x80000000u : 0u);
-            nn[(size_t)i * t.n_pc + t.cls_of[e]] = b->sectors[b->p_basis_sector[it->second]].nn;
+    for (int i = 0; i < n_t; ++i) {
+        int tm = 0, par = 1, c = 0;
+        for (uint32_t r = ts[i]; r; r &= r - 1) tm += ms[__builtin_ctz(r)].two_m, par *= ms[__builtin_ctz(r)].parity;
+        for (auto &q : cls) {
+            auto it = cols.find({tm + q.first.first, par * q.first.second});
+            if (it != cols.end()) nn[(size_t)i * t.n_pc + c] = it->second;
+            ++c;
         }
+    }
     auto cost = [&](int i, int c) -> int64_t {
         const int nt = (t.pc_first[c + 1] - t.pc_first[c] + 15) / 16;
         return (int64_t)nn[(size_t)i * t.n_pc + c] * 256 * nt * nt;
@@ -317,6 +317,16 @@ void build_pair_tables(fotci_ham *h) {
     for (int c = 0; c < t.n_pc; ++c)
         for (int i = 0; i < n_t; ++i) mine += cost(i, c);
     if (mine > dense) return;
+    std::vector<uint32_t> base((size_t)n_t * npairs, kCoreNoRow);
+    for (int i = 0; i < n_t; ++i)
+        for (size_t e = 0; e < st.size(); ++e) {
+            const uint32_t add = (1u << st[e].first) | (1u << st[e].second);
+            if ((ts[i] & add) || nn[(size_t)i * t.n_pc + t.cls_of[e]] == 0) continue;
+            auto it = std::lower_bound(idx.begin(), idx.end(), std::make_pair(ts[i] | add, (int32_t)0));
+            if (it == idx.end() || it->first != (ts[i] | add)) continue;
+            const bool odd = odd_below(ts[i], st[e].first) != odd_below(ts[i], st[e].second);
+            base[(size_t)i * npairs + t.pc_pair[e]] = (uint32_t)b->pstart[it->second] | (odd ? 0x80000000u : 0u);
+        }
     std::vector<std::pair<int64_t, std::array<int32_t, 3>>> vt;
     const int64_t share = std::max<int64_t>(mine / kPairsTasks, 1 << 16);
     for (int c = 0; c < t.n_pc; ++c) {

@@ -211,6 +211,7 @@ void build_tiled_tables(fotci_ham *h) {
         std::vector<std::vector<uint32_t>> lanes(64);
         std::vector<int> lane_order(64);
         std::vector<char> used_pairs;
+        std::vector<int32_t> where((size_t)t.max_nn + 1, -1);   // destination column -> its place in bydst
         auto pack = [&](int nr) -> bool {
             for (auto &l : lanes) l.clear();
             if ((int)used_pairs.size() < (nr + 1) / 2) used_pairs.resize((nr + 1) / 2);
@@ -253,18 +254,17 @@ void build_tiled_tables(fotci_ham *h) {
         for (size_t sl = 0; sl + 1 < cnt.size(); ++sl) {
             ptr[sl] = (int32_t)codes.size();
             if (cnt[sl] == cnt[sl + 1]) continue;
+            for (auto &d : bydst) where[d.first] = -1;
             bydst.clear();
-            std::map<uint32_t, size_t> where;
             for (int64_t k = cnt[sl]; k < cnt[sl + 1]; ++k) {
                 const auto &r = rec[order[k]];
                 const uint32_t dcol = (uint32_t)b->n.sd_local[r.dst];
                 const uint32_t code = code_of(r);
-                auto it = where.find(dcol);
-                if (it == where.end()) {
-                    where[dcol] = bydst.size();
+                if (where[dcol] < 0) {
+                    where[dcol] = (int32_t)bydst.size();
                     bydst.push_back({dcol, {code}});
                 } else {
-                    bydst[it->second].second.push_back(code);
+                    bydst[where[dcol]].second.push_back(code);
                 }
             }
             std::stable_sort(bydst.begin(), bydst.end(), [](const auto &x, const auto &y) {
@@ -674,13 +674,31 @@ extern "C" int fotci_ham_upload_impl(fotci_ham *h, void *ws, int64_t bytes, void
     if (((uintptr_t)ws & 255u) != 0) fail(FOTCI_EINVAL, "workspace must be 256-byte aligned");
     if (bytes < h->layout_total) fail(FOTCI_ENOMEM, "workspace smaller than fotci_ham_workspace_bytes");
     hipStream_t st = (hipStream_t)stream;
+    // Small tables lie next to each other: a run of them goes up as one copy
+    // (some eighty copies at a few microseconds each otherwise). Kept until the
+    // synchronisation below.
+    constexpr size_t kSmall = 1 << 16;
+    std::vector<std::pair<int64_t, std::vector<char>>> runs;
     int64_t off = 0;
+    bool open = false;
     for (auto &x : items(h)) {
         off = align256(off);
         *x.dev = (char *)ws + off;
-        if (x.host && x.bytes) hip_check(hipMemcpyAsync(*x.dev, x.host, x.bytes, hipMemcpyHostToDevice, st), "upload");
+        if (x.host && x.bytes && x.bytes <= kSmall) {
+            if (!open) runs.push_back({off, {}});
+            open = true;
+            auto &r = runs.back();
+            r.second.resize((size_t)(off - r.first) + x.bytes);
+            std::memcpy(r.second.data() + (off - r.first), x.host, x.bytes);
+        } else if (x.bytes) {
+            open = false;
+            if (x.host) hip_check(hipMemcpyAsync(*x.dev, x.host, x.bytes, hipMemcpyHostToDevice, st), "upload");
+        }
         off += (int64_t)x.bytes;
     }
+    for (auto &r : runs)
+        hip_check(hipMemcpyAsync((char *)ws + r.first, r.second.data(), r.second.size(), hipMemcpyHostToDevice, st),
+                  "upload");
     h->ws = ws;
     h->ws_bytes = bytes;
     launch_materialize(h, stream);
