@@ -43,7 +43,8 @@ def kernel_source_hash():
     code, table builder, shared layout constants): stored PMC traffic is used
     only for exactly these sources."""
     h = hashlib.sha256()
-    for f in ("kernels_tiled.hip", "tiled_common.h", "host_ham.cpp", "fotci_internal.h"):
+    for f in ("kernels_tiled.hip", "kernels_pn_cores.hip", "tiled_common.h", "host_ham.cpp", "host_cores.cpp",
+              "fotci_internal.h"):
         h.update(open(os.path.join(ROOT, "paper_1801_08432_amd", "csrc", f), "rb").read())
     return h.hexdigest()[:16]
 
@@ -376,7 +377,11 @@ def main():
                                     note="one x element per pn operation + y + tables; not HBM traffic "
                                          "(x is reused from LDS and matrix-core operands), so its GB/s can "
                                          "exceed the HBM peak"))
-    if dom == "k_pn":
+    # the counts of the jump kernels' lists; the core kernels' matrix-core
+    # instructions are in profiles/pn_counters_pf_5p5n.txt
+    cores = fotci.lib().fotci_apply_work_bytes(h._h, fotci.MODES[mode], 1) > 0
+    roof["pn_kernel"] = "k_pn_core" if cores else ("k_pn" if f64 else "k_pn2")
+    if dom == "k_pn" and not cores:
         pw = h.pn_work(mode)
         mf = pw["mfma_instr"] * MFMA_FLOPS_PER_INSTR / t_dom / 1e12
         roof["mfma"] = dict(instr_per_launch=pw["mfma_instr"], executed_tflops=round(mf, 2),
