@@ -427,6 +427,7 @@ int fotci_ham_pn_work(const fotci_ham *h, int32_t mode, int64_t *tile_visits, in
  * updated by plain LDS read-modify-write (when the row fits); 0 lets both
  * waves add to the row with LDS atomics, as the float64 kernel does. Both
  * give the same sums up to rounding order; the choice changes speed only.
+ * Products with work memory (fotci_apply_H_work) do not run these kernels.
  * FOTCI_EINVAL unless enable is 0 or 1. */
 int fotci_ham_set_pn_private_rows(fotci_ham *h, int32_t enable);
 

@@ -107,3 +107,25 @@ def test_one_body_densities_match_the_oracle(shape):
     rp, rn = ham.one_body_density(torch.tensor(g, device="cuda"), torch.tensor(x, device="cuda"))
     for got, ref in zip((rp, rn), fast.one_body_densities(prep, g, x)):
         assert np.linalg.norm(got.cpu().numpy() - ref) <= 1e-13 * max(np.linalg.norm(ref), 1.0)
+
+
+@pytest.mark.parametrize("mode", ["f32", "f64"])
+def test_apply_replays_from_a_graph(mode):
+    """The product and its work memory captured together; replays on new vectors, with eager products between."""
+    ham, _, _ = _case(SHAPES[4])
+    dt = torch.float32 if mode == "f32" else torch.float64
+    x = torch.randn(ham.dim, dtype=dt, device="cuda")
+    y = torch.empty_like(x)
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        ham.apply(x, y, mode=mode)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        ham.apply(x, y, mode=mode)
+    for _ in range(4):
+        x.copy_(torch.randn_like(x))
+        graph.replay()
+        ref = ham.apply(x, mode=mode)
+        torch.cuda.synchronize()
+        assert float((y - ref).double().norm()) <= 1e-14 * float(ref.double().norm())
