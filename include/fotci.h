@@ -221,7 +221,8 @@ int fotci_apply_H_block(const fotci_ham *h, int32_t mode, int32_t n_block, const
  * kernels: contributions to a row of y from its Z protons are summed in Z
  * slots of the work memory. work: device memory of at least
  * fotci_apply_work_bytes(h, mode, n_block) bytes, 16-byte aligned, not
- * overlapping x or y; it is overwritten and must not be used by other work
+ * overlapping x or y (nor may these overlap each other, n_block 1 included:
+ * FOTCI_EINVAL); it is overwritten and must not be used by other work
  * until the call's kernels have run on `stream`, and calls that may overlap in
  * time need one each. NULL (or a query of 0: the basis or mode has no such
  * kernels) runs the kernels of fotci_apply_H. Arguments, errors and results

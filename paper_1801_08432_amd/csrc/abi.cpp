@@ -220,7 +220,7 @@ int fotci_apply_H_work(const fotci_ham *h, int32_t mode, int32_t n_block, const 
         const int64_t bytes = h->j->b->dim * n_block * es;
         const char *xa = (const char *)x, *ya = (const char *)y, *wa = (const char *)work;
         auto overlap = [](const char *a, int64_t na, const char *b, int64_t nb) { return a < b + nb && b < a + na; };
-        if (n_block > 1 ? overlap(xa, bytes, ya, bytes) : xa == ya) fail(FOTCI_EINVAL, "x and y must not overlap");
+        if (xa == ya || overlap(xa, bytes, ya, bytes)) fail(FOTCI_EINVAL, "x and y must not overlap");
         if (wa && (overlap(xa, bytes, wa, need) || overlap(ya, bytes, wa, need)))
             fail(FOTCI_EINVAL, "work must not overlap x or y");
         launch_apply_nb(h, mode, n_block, x, y, stream, work);
