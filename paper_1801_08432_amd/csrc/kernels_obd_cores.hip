@@ -4,6 +4,10 @@
 //   rho_n[b, d] = sum_w phase sum_r g[r, w + b] x[r, w + d],
 // so a block of 4 x 4 entries takes eight loads per element pair (u, column) or
 // (row, w) and its sums stay in registers; a row dot per jump reads 2 for one.
+// A state that does not fit a core loads zeros, and 0 times an infinity or NaN
+// of its partner is NaN: a task whose sum is not finite takes it again over the
+// cores that both states fit. (Leaving those products out of the loops
+// themselves took 0.66 ms at pf 5p5n instead of 0.64.)
 #include <hip/hip_runtime.h>
 
 #include "tiled_common.h"
@@ -14,9 +18,14 @@ namespace {
 
 constexpr int kOcThreads = 256, kOcWaves = kOcThreads / 64;
 
-// adds the workgroup's 4 x 4 sums to rho; b, d: states of this block's rows and columns (-1: none)
+// Adds the workgroup's 4 x 4 sums to rho; b, d: states of this block's rows and
+// columns (-1: none). each(b, d): one entry's sum over the cores that both
+// states fit, a share per lane of one wave (the others are gone by then: a
+// second barrier for them took 104 us at pf 4p4n, which is short workgroups,
+// instead of 79).
+template <typename F>
 __device__ __forceinline__ void oc_finish(double (&acc)[4][4], const int (&b)[4], const int (&d)[4], int ns, int lane,
-                                          int wid, double (*lds)[16], double *rho) {
+                                          int wid, double (*lds)[16], double *rho, F each) {
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
@@ -26,13 +35,26 @@ __device__ __forceinline__ void oc_finish(double (&acc)[4][4], const int (&b)[4]
             if (lane == 0) lds[wid][4 * i + j] = v;
         }
     __syncthreads();
-    if (threadIdx.x < 16) {
+    if (wid != 0) return;
+    bool again = false;
+    int at = 0;
+    if (lane < 16) {
         double v = 0.0;
-        for (int w = 0; w < kOcWaves; ++w) v += lds[w][threadIdx.x];
-        const int i = threadIdx.x >> 2, j = threadIdx.x & 3;
+        for (int w = 0; w < kOcWaves; ++w) v += lds[w][lane];
+        const int i = lane >> 2, j = lane & 3;
         const int bi = i == 0 ? b[0] : i == 1 ? b[1] : i == 2 ? b[2] : b[3];
         const int dj = j == 0 ? d[0] : j == 1 ? d[1] : j == 2 ? d[2] : d[3];
-        if (bi >= 0 && dj >= 0) atomicAdd(&rho[bi * ns + dj], v);
+        if (bi >= 0 && dj >= 0) {
+            at = bi * ns + dj;
+            again = v - v != 0.0;
+            if (!again) atomicAdd(&rho[at], v);
+        }
+    }
+    for (uint64_t m = __ballot(again); m; m &= m - 1) {
+        const int e = __shfl(at, __builtin_ctzll(m), 64);
+        double v = each(e / ns, e % ns);
+        for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+        if (lane == 0) atomicAdd(&rho[e], v);
     }
 }
 
@@ -94,7 +116,18 @@ __global__ __launch_bounds__(kOcThreads) void k_obd_p(DevHam P, DevCore C, const
                 for (int j = 0; j < 4; ++j) acc[i][j] += gv[i] * xv[j];
         }
     }
-    oc_finish(acc, b, d, C.ns, lane, wid, lds, rho);
+    oc_finish(acc, b, d, C.ns, lane, wid, lds, rho, [&](int bi, int dj) {
+        double sum = 0.0;
+        for (int u = t[2]; u < u1; ++u) {
+            const uint32_t rb = C.u_base[(int64_t)u * C.ns + bi], rd = C.u_base[(int64_t)u * C.ns + dj];
+            if (rb == kCoreNoRow || rd == kCoreNoRow) continue;
+            const int nn = C.u_nn[(int64_t)u * C.ns + bi];
+            for (int c = lane; c < nn; c += 64)
+                sum += signed_by(buffer_load<double>(gr, (rb << 3) + 8u * c, 0), rb) *
+                       signed_by(buffer_load<double>(xr, (rd << 3) + 8u * c, 0), rd);
+        }
+        return sum;
+    });
 }
 
 // task {class, block, basis sector, first core of the neutron group, first
@@ -144,7 +177,16 @@ __global__ __launch_bounds__(kOcThreads) void k_obd_n(DevHam P, DevCore C, const
     for (int i = 0; i < 4; ++i)
 #pragma unroll
         for (int k = 0; k < 4; ++k) acc[i][k] = signed_by(acc[i][k], cb[i] ^ cd[k]);
-    oc_finish(acc, b, d, C.ns, lane, wid, lds, rho);
+    oc_finish(acc, b, d, C.ns, lane, wid, lds, rho, [&](int bi, int dj) {
+        double sum = 0.0;
+        const uint32_t vb = j < wpad ? code[bi * wpad + j] : core_null(3), vd = j < wpad ? code[dj * wpad + j] : core_null(3);
+        if (max(vb & 0x7fffffffu, vd & 0x7fffffffu) >= core_null(3)) return sum;
+        for (int r = r0; r < min(r0 + kObdRows, np); ++r) {
+            const unsigned ro = (unsigned)(base + (int64_t)r * nn) * 8u;
+            sum += buffer_load<double>(gr, ro + (vb << 3), 0) * buffer_load<double>(xr, ro + (vd << 3), 0);
+        }
+        return signed_by(sum, vb ^ vd);
+    });
 }
 
 }  // namespace
