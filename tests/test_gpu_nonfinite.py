@@ -57,3 +57,19 @@ def test_one_body_densities_keep_nonfinite_elements_to_their_entries(shape, wher
         got = ham.one_body_density(torch.tensor(g, device="cuda"), torch.tensor(x, device="cuda"))
         for a, b in zip(got, fast.one_body_densities(prep, g, x)):
             _same(a.cpu().numpy(), b)
+
+
+def _labels(shape, where, value, keys):
+    ham, prep = _case(shape)
+    for seed in range(4):
+        x, g = _vectors(ham.dim, where, value, seed)
+        _, grads = ham.vjp(torch.tensor(x, device="cuda"), torch.tensor(g, device="cuda"))
+        ref = fast.densities(prep, g, x)
+        for k in keys:
+            _same(grads[k].cpu().numpy(), ref["d_" + k])
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=str)
+@pytest.mark.parametrize("where,value", VALUES)
+def test_like_particle_label_densities_keep_nonfinite_elements_to_their_entries(shape, where, value):
+    _labels(shape, where, value, ("v_pp", "v_nn", "eps_p", "eps_n"))
