@@ -102,16 +102,22 @@ __global__ __launch_bounds__(64 * kVtWaves) void k_vjp_pairs(DevHam P, DevPairs 
         default: vt_task<3>(P, C, n, p0, i0, i1, xr, gr, wid, lane, red); break;
     }
     __syncthreads();
+    bool again = false;
+    for (int i = tid; i < n * n; i += 64 * kVtWaves) {
+        const int p = i / n, q = i - p * n;
+        const double v = red[p * (16 * nt) + q];
+        if (v - v != 0.0) again = true;
+        else if (v != 0.0) atomicAdd(&d_v[(int64_t)C.pc_pair[p0 + p] * P.npairs + C.pc_pair[p0 + q]], v);
+    }
+    // A row that does not exist is a row of zeros above, and 0 times an infinity
+    // or NaN is NaN: sums that are not finite are taken again, a wave for each,
+    // over the t that both pairs fit.
+    if (!__any(again)) return;
     for (int base = 64 * wid; base < n * n; base += 64 * kVtWaves) {
-        const int i = base + lane, p = i / n, q = i - p * n;
-        const double v = i < n * n ? red[p * (16 * nt) + q] : 0.0;
-        const int pr = i < n * n ? C.pc_pair[p0 + p] : 0, pq = i < n * n ? C.pc_pair[p0 + q] : 0;
-        const bool again = v - v != 0.0;
-        if (v != 0.0 && !again) atomicAdd(&d_v[(int64_t)pr * P.npairs + pq], v);
-        // A row that does not exist is a row of zeros above, and 0 times an
-        // infinity or NaN is NaN: sums that are not finite are taken again, a
-        // wave for each, over the t that both pairs fit.
-        for (uint64_t m = __ballot(again); m; m &= m - 1) {
+        const int i = min(base + lane, n * n - 1), p = i / n, q = i - p * n;
+        const double v = red[p * (16 * nt) + q];
+        const int pr = C.pc_pair[p0 + p], pq = C.pc_pair[p0 + q];
+        for (uint64_t m = __ballot(v - v != 0.0 && base + lane < n * n); m; m &= m - 1) {
             const int l = __builtin_ctzll(m), rp = __shfl(pr, l, 64), rq = __shfl(pq, l, 64);
             double sum = 0.0;
             for (int t = i0; t < i1; ++t) {

@@ -73,3 +73,9 @@ def _labels(shape, where, value, keys):
 @pytest.mark.parametrize("where,value", VALUES)
 def test_like_particle_label_densities_keep_nonfinite_elements_to_their_entries(shape, where, value):
     _labels(shape, where, value, ("v_pp", "v_nn", "eps_p", "eps_n"))
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=str)
+@pytest.mark.parametrize("where,value", VALUES)
+def test_pn_label_densities_keep_nonfinite_elements_to_their_entries(shape, where, value):
+    _labels(shape, where, value, ("v_pn",))
