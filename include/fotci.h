@@ -440,7 +440,8 @@ int fotci_ham_set_pn_private_rows(fotci_ham *h, int32_t enable);
  * most; later calls are not recorded). stop synchronises on the events and
  * writes, for each kernel of the last recorded mode, the mean duration in
  * milliseconds (avg_ms[k], k < *n_kernels <= 4) and its name (names[k],
- * static strings; names may be NULL); *n_calls = calls recorded. The events
+ * static strings; names may be NULL), in the order diagonal + nn, pp, pn
+ * whichever ran first; *n_calls = calls recorded. The events
  * are host-side HIP objects created by start and destroyed by stop.
  */
 int fotci_profile_start(fotci_ham *h, int32_t max_calls);

@@ -367,6 +367,8 @@ int fotci_profile_start(fotci_ham *h, int32_t max_calls) {
         pr.max_calls = max_calls;
         pr.calls = 0;
         pr.n_kernels = 0;
+        pr.order.clear();
+        pr.order.reserve((size_t)max_calls);
         pr.on = true;
         return FOTCI_OK;
     });
@@ -378,17 +380,20 @@ int fotci_profile_stop(fotci_ham *h, double *avg_ms, const char **names, int32_t
         auto &pr = h->prof;
         pr.on = false;
         double acc[4] = {0, 0, 0, 0};
+        int same = 0;   // calls with as many kernels as the last
         for (int c = 0; c < pr.calls; ++c) {
+            if (pr.order[c].n_kernels != pr.n_kernels) continue;
+            ++same;
             void **ev = &pr.events[(size_t)c * 5];
             hip_check(hipEventSynchronize((hipEvent_t)ev[pr.n_kernels]), "hipEventSynchronize");
             for (int k = 0; k < pr.n_kernels; ++k) {
                 float ms = 0.f;
                 hip_check(hipEventElapsedTime(&ms, (hipEvent_t)ev[k], (hipEvent_t)ev[k + 1]), "hipEventElapsedTime");
-                acc[k] += ms;
+                acc[pr.order[c].pn_first ? (k + 2) % 3 : k] += ms;   // pn is the third part
             }
         }
         for (int k = 0; k < pr.n_kernels; ++k) {
-            if (avg_ms) avg_ms[k] = pr.calls ? acc[k] / pr.calls : 0.0;
+            if (avg_ms) avg_ms[k] = same ? acc[k] / same : 0.0;
             if (names) names[k] = pr.names[k];
         }
         if (n_kernels) *n_kernels = pr.n_kernels;

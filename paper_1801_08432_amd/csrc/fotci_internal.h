@@ -354,6 +354,18 @@ struct fotci_ham {
         int max_calls = 0, calls = 0, n_kernels = 0;
         std::vector<void *> events;   // hipEvent_t, (max_calls * 5)
         const char *names[4] = {nullptr, nullptr, nullptr, nullptr};
+        struct Call {
+            int n_kernels;
+            bool pn_first;   // the pn part ran before nn and pp (with work memory), not after
+        };
+        std::vector<Call> order;   // of every recorded call
+        // a recorded call of one kernel, or of the nn, pp and pn parts
+        void record(std::initializer_list<const char *> parts, bool pn_first) {
+            n_kernels = 0;
+            for (const char *p : parts) names[n_kernels++] = p;
+            order.push_back({n_kernels, pn_first});
+            ++calls;
+        }
     };
     mutable Profile prof;
     // layout (offsets in bytes from ws), filled by layout()

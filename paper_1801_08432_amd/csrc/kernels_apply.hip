@@ -169,23 +169,17 @@ void launch_apply(const fotci_ham *h, int mode, const void *x, void *y, void *st
             launch_apply_plain(h->dev, mode, x, y, stream);
             if (ev) {
                 hip_check(hipEventRecord((hipEvent_t)ev[1], (hipStream_t)stream), "event");
-                pr.n_kernels = 1;
-                pr.names[0] = "k_apply_plain";
+                pr.record({"k_apply_plain"}, false);
             }
             break;
         case FOTCI_MODE_F64:
         case FOTCI_MODE_F32:
             launch_apply_tiled(h, mode, x, y, stream, ev, work);
-            if (ev) {
-                pr.n_kernels = 3;
-                static const char *const order[2][3] = {{"k_nn_diag", "k_pp", "k_pn"}, {"k_pn", "k_nn_diag", "k_pp"}};
-                for (int k = 0; k < 3; ++k) pr.names[k] = order[work ? 1 : 0][k];
-            }
+            if (ev) pr.record({"k_nn_diag", "k_pp", "k_pn"}, work != nullptr);
             break;
         default:
             fail(FOTCI_EINVAL, "unknown or unsupported mode");
     }
-    if (ev) pr.calls++;
 }
 
 void launch_apply_nb(const fotci_ham *h, int mode, int nb, const void *x, void *y, void *stream, void *work) {
@@ -197,12 +191,7 @@ void launch_apply_nb(const fotci_ham *h, int mode, int nb, const void *x, void *
     void **ev = nullptr;
     if (pr.on && pr.calls < pr.max_calls) ev = &pr.events[(size_t)pr.calls * 5];
     launch_apply_block(h, mode, nb, x, y, stream, ev, work);
-    if (ev) {
-        pr.n_kernels = 3;
-        static const char *const order[2][3] = {{"k_nn_diag_blk", "k_pp_blk", "k_pn"}, {"k_pn", "k_nn_diag_blk", "k_pp_blk"}};
-        for (int k = 0; k < 3; ++k) pr.names[k] = order[work ? 1 : 0][k];
-        pr.calls++;
-    }
+    if (ev) pr.record({"k_nn_diag_blk", "k_pp_blk", "k_pn"}, work != nullptr);
 }
 
 }  // namespace fotci
