@@ -47,18 +47,22 @@ __global__ __launch_bounds__(kT) void k_zero(double *p, int n) {
 }
 
 // The diagonal. Row dots <g[ip, :], x[ip, :]> of the proton rows: a wave per
-// row, kDiagRows rows per workgroup, whose orbit and diagonal-label sums meet in
+// row, some rows per workgroup, whose orbit and diagonal-label sums meet in
 // LDS before they are added to the result (one atomic per row and label on a
 // few hundred addresses, and one per element for the column sums, ran at 0.98
-// + 0.95 ms at pf 5p5n for both species).
-constexpr int kDiagRows = 32, kDiagPairs = 496, kDiagOrbs = 32;   // 32 m-states at most
-__device__ __forceinline__ void diag_add(double dd, int i, const DevSpecies &S, const DevHam &P, double *orb, double *lab,
-                                         bool want_lab) {
-    const uint32_t m = S.masks[i];
-    for (uint32_t r = m; r; r &= r - 1)
-        __hip_atomic_fetch_add(&orb[P.ms_orbit[__builtin_ctz(r)]], dd, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+// + 0.95 ms at pf 5p5n for both species). The lanes share a row's labels: an SD
+// near a full shell has some hundred and fifty, which one lane takes 0.36 ms
+// to add (20 states, 18p18n; the labels of a neutron SD 0.06 ms).
+constexpr int kDiagPairs = 496, kDiagOrbs = 32;   // 32 m-states at most
+// Rows of a workgroup: enough workgroups for the chip where there are few rows,
+// few flushes of the label sums where there are many.
+inline int diag_rows(int n_sd) { return std::min(32, std::max(4, (n_sd + 511) / 512)); }
+__device__ __forceinline__ void diag_add(double dd, int i, int lane, const DevSpecies &S, const DevHam &P, double *orb,
+                                         double *lab, bool want_lab) {
+    if (lane < P.ns && ((S.masks[i] >> lane) & 1u))
+        __hip_atomic_fetch_add(&orb[P.ms_orbit[lane]], dd, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     if (want_lab)
-        for (int j = S.diag_j0[i]; j < S.diag_j1[i]; ++j) {
+        for (int j = S.diag_j0[i] + lane; j < S.diag_j1[i]; j += 64) {
             const int code = S.code2[j];   // a diagonal label is pair * (n_pairs + 1)
             __hip_atomic_fetch_add(&lab[(code >> 1) / (P.npairs + 1)], (code & 1) ? -dd : dd, __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -72,8 +76,8 @@ __device__ __forceinline__ void diag_flush(const double *orb, const double *lab,
     for (int i = threadIdx.x; i < P.npairs; i += kT)
         if (d_v && lab[i] != 0.0) atomicAdd(&d_v[(int64_t)i * (P.npairs + 1)], lab[i]);
 }
-__global__ __launch_bounds__(kT) void k_diag_rows(DevHam P, const double *__restrict__ x, const double *__restrict__ g,
-                                                  double *d_spe_p, double *d_v_pp) {
+__global__ __launch_bounds__(kT) void k_diag_rows(DevHam P, int rows, const double *__restrict__ x,
+                                                  const double *__restrict__ g, double *d_spe_p, double *d_v_pp) {
     __shared__ double orb[kDiagOrbs], lab[kDiagPairs];
     for (int i = threadIdx.x; i < kDiagPairs; i += kT) {
         lab[i] = 0.0;
@@ -81,15 +85,15 @@ __global__ __launch_bounds__(kT) void k_diag_rows(DevHam P, const double *__rest
     }
     __syncthreads();
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    const int end = min((int)(blockIdx.x + 1) * kDiagRows, P.p.n_sd);
-    for (int ip = blockIdx.x * kDiagRows + wid; ip < end; ip += kT / 64) {
+    const int end = min((int)(blockIdx.x + 1) * rows, P.p.n_sd);
+    for (int ip = blockIdx.x * rows + wid; ip < end; ip += kT / 64) {
         const int nn = P.sec_nn[P.p_sector[ip]];
         const int64_t base = P.p_pstart[ip];
         double acc = 0.0;
 #pragma unroll 4
         for (int c = lane; c < nn; c += 64) acc += g[base + c] * x[base + c];
         acc = wave_sum(acc);
-        if (lane == 0) diag_add(acc, ip, P.p, P, orb, lab, d_v_pp != nullptr);
+        diag_add(acc, ip, lane, P.p, P, orb, lab, d_v_pp != nullptr);
     }
     diag_flush(orb, lab, P, d_spe_p, d_v_pp);
 }
@@ -112,15 +116,18 @@ __global__ __launch_bounds__(kT) void k_diag_cols(DevHam P, const double *__rest
     for (int r = r0; r < r1; ++r) acc += g[at + (int64_t)r * nn] * x[at + (int64_t)r * nn];
     atomicAdd(&dcol[jn], acc);
 }
-__global__ __launch_bounds__(kT) void k_diag_neutron(DevHam P, const double *dcol, double *d_spe_n, double *d_v_nn) {
+__global__ __launch_bounds__(kT) void k_diag_neutron(DevHam P, int rows, const double *dcol, double *d_spe_n,
+                                                     double *d_v_nn) {
     __shared__ double orb[kDiagOrbs], lab[kDiagPairs];
     for (int i = threadIdx.x; i < kDiagPairs; i += kT) {
         lab[i] = 0.0;
         if (i < kDiagOrbs) orb[i] = 0.0;
     }
     __syncthreads();
-    const int jn = blockIdx.x * kT + threadIdx.x;
-    if (jn < P.n.n_sd && P.n_bsector[jn] >= 0) diag_add(dcol[jn], jn, P.n, P, orb, lab, d_v_nn != nullptr);
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    const int end = min((int)(blockIdx.x + 1) * rows, P.n.n_sd);
+    for (int jn = blockIdx.x * rows + wid; jn < end; jn += kT / 64)
+        if (P.n_bsector[jn] >= 0) diag_add(dcol[jn], jn, lane, P.n, P, orb, lab, d_v_nn != nullptr);
     diag_flush(orb, lab, P, d_spe_n, d_v_nn);
 }
 
@@ -624,15 +631,17 @@ void launch_vjp(const DevHam &d, const fotci_ham *h, const double *x, const doub
     const bool pairs = d_v_pp && launch_vjp_pairs(h, x, g, d_v_pp, stream);   // every pp label
     const bool sd_p = d_v_pp && tt.ok && !pairs, sd_n = d_v_nn && tt.ok;
     if (d_spe_p || (d_v_pp && !pairs))
-        hipLaunchKernelGGL(k_diag_rows, dim3((d.p.n_sd + kDiagRows - 1) / kDiagRows), dim3(kT), 0, st, d, x, g, d_spe_p,
-                           pairs ? (double *)nullptr : d_v_pp);
+        hipLaunchKernelGGL(k_diag_rows, dim3((d.p.n_sd + diag_rows(d.p.n_sd) - 1) / diag_rows(d.p.n_sd)), dim3(kT), 0, st, d,
+                           diag_rows(d.p.n_sd), x, g, d_spe_p, pairs ? (double *)nullptr : d_v_pp);
     if (need_n) {
         int max_np = 1;
         for (int v : h->tc.sec_np) max_np = std::max(max_np, v);
         const unsigned cols = (unsigned)((d.n.n_sd + kT - 1) / kT);
         hipLaunchKernelGGL(k_diag_cols, dim3(cols, (max_np + kDiagColRows - 1) / kDiagColRows), dim3(kT), 0, st, d, x, g,
                            dcol);
-        hipLaunchKernelGGL(k_diag_neutron, dim3(cols), dim3(kT), 0, st, d, (const double *)dcol, d_spe_n, d_v_nn);
+        const int rows = diag_rows(d.n.n_sd);
+        hipLaunchKernelGGL(k_diag_neutron, dim3((d.n.n_sd + rows - 1) / rows), dim3(kT), 0, st, d, rows, (const double *)dcol,
+                           d_spe_n, d_v_nn);
     }
     if (d_v_pp && !pairs && !sd_p) hipLaunchKernelGGL(k_vjp_off<false>, dim3(d.p.n_sd), dim3(kT), 0, st, d, x, g, d_v_pp);
     if (d_v_nn && !sd_n) hipLaunchKernelGGL(k_vjp_off<true>, dim3(d.n.n_sd), dim3(kT), 0, st, d, x, g, d_v_nn);
