@@ -157,6 +157,7 @@ constexpr int kObdCores = 32;       // proton cores of a density task
 constexpr int kObdRows = 256;       // proton rows of one
 constexpr uint32_t kCoreNoRow = 0xffffffffu;
 constexpr int kCoreMaxPc = 64;      // pair classes
+constexpr int kCoreMaxPairs = 64;   // pairs of a class
 constexpr int kCoreStates = 8;      // added states of a work item
 constexpr int kCoreMaxPos = 32;     // positions (a state a with up to four states b) of an item in a class
 constexpr int kCoreRowElems = 14336;   // row elements of a work item in LDS (float64)
@@ -263,7 +264,8 @@ struct DevTiled {
 
 // Host side of DevCore.
 struct HostCore {
-    bool ok = false;
+    bool ok = false;      // cores, rows, codes of float64 vectors and the densities' tables are there
+    bool apply = false;   // and those of the products; v_tasks is empty where the label densities run on jumps
     int n_pc = 0, w_null = 0;
     std::vector<uint32_t> u_mask;
     std::vector<int32_t> u_group, u_nn, w_of, w_n, w_pad, w_off, pc_n, pc_pair, pc_v, pc_first, pair_ab;
@@ -406,11 +408,16 @@ bool launch_vjp_pairs(const fotci_ham *h, const double *x, const double *g, doub
 // the core kernels, 0 where it does not use them: one slot of dim * nb elements
 // per proton.
 int64_t apply_work_bytes(const fotci_ham *h, int mode, int nb);
+// LDS of the matrix-core jump kernel of the pn label densities, and whether it can run
+inline size_t vjp_jump_lds(int max_nn) {
+    return ((size_t)((max_nn + 2) & ~1) + (size_t)kPnWaves * kPnTile * kPnRStride) * sizeof(double);
+}
+inline bool vjp_pn_jumps(const fotci_ham *h) { return h->tt.ok && vjp_jump_lds(h->tt.max_nn) <= 65536; }
 // pn part into the slots
 void launch_pn_cores(const fotci_ham *h, int mode, int nb, const void *x, void *slots, void *stream);
 // pn label densities on the cores (added to d_v_pn); false where another kernel
-// is to do it. jumps: the matrix-core jump kernel could.
-bool launch_vjp_cores(const fotci_ham *h, const double *x, const double *g, double *d_v_pn, bool jumps, void *stream);
+// is to do it
+bool launch_vjp_cores(const fotci_ham *h, const double *x, const double *g, double *d_v_pn, void *stream);
 void launch_one_body_density(const fotci_ham *h, int q0, const double *g, const double *x, double *rho_p,
                              double *rho_n, void *stream);
 // adds the densities to rho_p and rho_n (null: not wanted); needs hc.ok

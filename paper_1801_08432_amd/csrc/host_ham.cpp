@@ -554,7 +554,7 @@ std::vector<Item> items(fotci_ham *h) {
     DevCore &dc = h->dev_core;
     dc.n_pc = hc.n_pc;
     dc.ns = h->j->ns;
-    dc.n_w_code = (int32_t)hc.w_code[0].size();
+    dc.n_w_code = (int32_t)hc.w_code[3 - kCoreMinShift].size();
     dc.w_null = hc.w_null;
     dc.n_v = (int32_t)hc.v_src.size();
     add(hc.u_mask.data(), hc.u_mask.size() * 4, &dc.u_mask);

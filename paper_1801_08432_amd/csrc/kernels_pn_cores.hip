@@ -17,8 +17,6 @@
 // issue 41% of the time to the vector and 31% to the matrix units; without the
 // loads of x and its codes it still runs at 1.49 ms, without the matrix
 // instructions at 1.35 ms.
-#include <cmath>
-
 #include "tiled_common.h"
 
 namespace fotci {
@@ -30,8 +28,6 @@ constexpr int kCorePos = 4 * kCoreTiles;       // positions (a with up to four o
 constexpr int kCoreSlots = 56;                 // (c d) pairs per pass: 14 k-steps, three waves per SIMD
 constexpr int kCoreRowShift = 3;               // bytes of an LDS row element, log2
 constexpr int kCoreSub = 12;                   // 16-core subtiles per task
-constexpr int kCoreFewStates = 12;             // see apply_work_bytes
-constexpr double kCoreFewLine = 1.2;
 
 // Matrix row i of a tile: lane group g and accumulator element r that hold it.
 template <typename T>
@@ -389,42 +385,6 @@ void launch_cores(const fotci_ham *h, int nb, const T *x, T *slots, hipStream_t 
 }
 
 }  // namespace
-
-// The core kernels gather x, per element of y, for Z N pairs, of which a share
-// (N_s - N + 1) / N_s of the lanes hits a free state d, once for every group of
-// kCoreStates states a; the one-body-jump kernels gather N (N_s - N + 1) rows of
-// their contracted tile. Measured times of the two pn parts against the ratio
-// of these counts (jumps / cores): float32 2.84 / 1.65 ms at 1.28 (20 states,
-// 5p5n), 0.77 / 0.60 at 1.25 (3p6n), 2.14 / 2.48 at 0.78 (18 states, 8p4n), 4.4 /
-// 10.3 at 0.67 (5p8n); float64, whose row updates cost the jump kernel more,
-// 6.9 / 2.4, 1.85 / 0.78, 3.7 / 2.9 and 10.9 / 12.6. Shells beyond the middle
-// fall far below the line (20 states, 15p14n: 0.16).
-//
-// In spaces of up to kCoreFewStates states a task is one to four subtiles and an
-// item costs its set-up, whatever it gathers, while the jump kernel pays per row:
-// there the ratio is divided by the items per row, and by what a last round of
-// workgroups leaves idle. float64 takes the cores from kCoreFewLine on or where all
-// items run at once; float32, three workgroups a CU and cheaper registers, as
-// elsewhere. Measured, us of a product (12 states, float64, jumps / cores), by
-// the quotient: 49.8 / 68.6 at 0.40 (8p4n, blocks of 2), 44.7 / 51.6 at 0.59
-// (7p5n), 46.3 / 51.2 at 0.80 (6p5n), 69.8 / 72.1 at 1.0 (4p3n, blocks of 4), 41.9 /
-// 44.3 at 1.01 (6p4n), 80.1 / 72.2 at 1.26 (5p6n, blocks of 2); one round: 38.3 /
-// 32.7 (4p4n). In 16 and more states the cores win from quotients of 0.5 on (18
-// states, 8p4n: 4.77 / 3.82 ms).
-int64_t apply_work_bytes(const fotci_ham *h, int mode, int nb) {
-    if ((mode != FOTCI_MODE_F64 && mode != FOTCI_MODE_F32) || !h->hc.ok) return 0;
-    const double ns = h->j->ns, Z = h->j->b->p.n, N = h->j->b->n.n, open = ns - N + 1;
-    const double groups = std::ceil((ns - Z + 1) / kCoreStates);
-    const double ratio = N * open / (Z * N * ns / open * groups);
-    if (ratio < (mode == FOTCI_MODE_F64 ? 0.75 : 1.0)) return 0;
-    if (mode == FOTCI_MODE_F64 && ns <= kCoreFewStates) {
-        const double cores = (double)h->hc.u_mask.size() * groups, rows = (double)h->j->b->p.sd.size();
-        const double rounds = cores * nb / (256.0 * core_threads<double>() / 256);   // of four-wave workgroups
-        if (rounds > 1.0 && ratio * rows / cores * (rounds / std::ceil(rounds)) < kCoreFewLine) return 0;
-    }
-    const int64_t es = mode == FOTCI_MODE_F64 ? 8 : 4;
-    return h->j->b->dim * nb * es * h->j->b->p.n;
-}
 
 void launch_pn_cores(const fotci_ham *h, int mode, int nb, const void *x, void *slots, void *stream) {
     if (mode == FOTCI_MODE_F64)

@@ -653,12 +653,10 @@ void launch_vjp(const DevHam &d, const fotci_ham *h, const double *x, const doub
         const int64_t tiles = sddmm_tiles(true);
         if (tiles > 0) hipLaunchKernelGGL(k_vjp_sddmm<true>, dim3((unsigned)tiles), dim3(64), 0, st, d, tt, x, g, d_v_nn);
     }
-    const DevTiled &t = tt;
-    const size_t lds = ((size_t)((t.max_nn + 2) & ~1) + (size_t)kPnWaves * kPnTile * kPnRStride) * sizeof(double);
-    const bool jumps = t.ok && lds <= 65536;
-    if (d_v_pn && !launch_vjp_cores(h, x, g, d_v_pn, jumps, stream)) {
-        if (jumps) {
-            hipLaunchKernelGGL(k_vjp_pn_mfma, dim3(d.p.n_sd), dim3(kVjpThreads), lds, st, d, t, x, g, d_v_pn);
+    if (d_v_pn && !launch_vjp_cores(h, x, g, d_v_pn, stream)) {
+        if (vjp_pn_jumps(h)) {
+            hipLaunchKernelGGL(k_vjp_pn_mfma, dim3(d.p.n_sd), dim3(kVjpThreads), vjp_jump_lds(tt.max_nn), st, d, tt, x, g,
+                               d_v_pn);
         } else {
             for (int q = 0; q < d.nq; ++q)
                 if ((int64_t)h->j->cls.ops[q].size() * h->vq_nb[q] > kMaxBins)

@@ -176,18 +176,9 @@ __global__ __launch_bounds__(64 * kVcWaves) __attribute__((amdgpu_waves_per_eu(2
 
 }  // namespace
 
-// Per element of g the cores gather Z N pairs, of which a share (N_s - N + 1) /
-// N_s of the lanes finds a free state, the jump kernel scatters N (N_s - N + 1)
-// entries: measured, all densities, jumps against cores, by the ratio of the
-// counts: 17.4 / 10.5 ms at 2.6 (20 states, 5p5n), 0.40 / 0.34 at 0.7 (12 states, 6p6n),
-// 7.6 / 29.8 at 0.15 (18 states, 13p13n). Where a row and its tiles exceed the jump
-// kernel's LDS, what is left is one LDS atomic per pair of jumps (177 / 23.7 ms, 18
-// states, 5p8n).
-bool launch_vjp_cores(const fotci_ham *h, const double *x, const double *g, double *d_v_pn, bool jumps, void *stream) {
+bool launch_vjp_cores(const fotci_ham *h, const double *x, const double *g, double *d_v_pn, void *stream) {
     const int n = (int)(h->hc.v_tasks.size() / 3);
-    if (!h->hc.ok || n == 0) return false;
-    const double ns = h->j->ns, Z = h->j->b->p.n, N = h->j->b->n.n, open = ns - N + 1;
-    if (jumps && N * open < 0.6 * (Z * N * ns / open)) return false;
+    if (n == 0) return false;
     hipLaunchKernelGGL(k_vjp_pn_cores, dim3(n), dim3(64 * kVcWaves), 0, (hipStream_t)stream, h->dev, h->dev_core, x, g,
                        d_v_pn);
     return true;
