@@ -289,7 +289,8 @@ class Hamiltonian:
                 if stream is None:
                     work = torch.empty(n, dtype=torch.uint8, device=x.device)
                 else:
-                    with torch.cuda.stream(stream):
+                    own = isinstance(stream, torch.cuda.Stream)   # else: another library's, known by its handle
+                    with torch.cuda.stream(stream if own else torch.cuda.ExternalStream(stream.cuda_stream, x.device)):
                         work = torch.empty(n, dtype=torch.uint8, device=x.device)
             except torch.cuda.OutOfMemoryError:
                 n = 0

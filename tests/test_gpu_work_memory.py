@@ -209,3 +209,20 @@ def test_products_on_a_stream_of_the_callers():
     torch.cuda.synchronize()
     for v in range(2):
         assert float((Y[:, v] - want[v]).norm()) <= 1e-13 * float(want[v].norm())
+
+
+def test_a_stream_may_be_any_object_with_its_handle():
+    """As for every other call: the binding reads cuda_stream alone."""
+    class Handle:
+        pass
+
+    h = _ham("pf_4p4n")
+    x = torch.randn(h.dim, dtype=torch.float64, device=DEV)
+    want, s, side = h.apply(x), Handle(), torch.cuda.Stream()
+    s.cuda_stream = side.cuda_stream
+    torch.cuda.synchronize()
+    y = torch.empty_like(x)
+    torch.cuda.synchronize()
+    h.apply(x, y, stream=s)
+    torch.cuda.synchronize()
+    assert float((y - want).norm()) <= 1e-13 * float(want.norm())
