@@ -367,8 +367,7 @@ int fotci_profile_start(fotci_ham *h, int32_t max_calls) {
         pr.max_calls = max_calls;
         pr.calls = 0;
         pr.n_kernels = 0;
-        pr.order.clear();
-        pr.order.reserve((size_t)max_calls);
+        pr.order.assign((size_t)max_calls, {});
         pr.on = true;
         return FOTCI_OK;
     });

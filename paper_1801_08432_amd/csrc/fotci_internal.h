@@ -360,13 +360,12 @@ struct fotci_ham {
             int n_kernels;
             bool pn_first;   // the pn part ran before nn and pp (with work memory), not after
         };
-        std::vector<Call> order;   // of every recorded call
+        std::vector<Call> order;   // of every recorded call (max_calls)
         // a recorded call of one kernel, or of the nn, pp and pn parts
         void record(std::initializer_list<const char *> parts, bool pn_first) {
             n_kernels = 0;
             for (const char *p : parts) names[n_kernels++] = p;
-            order.push_back({n_kernels, pn_first});
-            ++calls;
+            order[calls++] = {n_kernels, pn_first};
         }
     };
     mutable Profile prof;
