@@ -209,7 +209,9 @@ void build_label_tasks(HostCore &t, int nu) {
 // 5p5n), 0.77 / 0.60 at 1.25 (3p6n), 2.14 / 2.48 at 0.78 (18 states, 8p4n), 4.4 /
 // 10.3 at 0.67 (5p8n); float64, whose row updates cost the jump kernel more,
 // 6.9 / 2.4, 1.85 / 0.78, 3.7 / 2.9 and 10.9 / 12.6. Shells beyond the middle
-// fall far below the line (20 states, 15p14n: 0.16).
+// fall far below the line (20 states, 15p14n: 0.16). The float32 figure at 0.78 is from
+// before the items' set-up was shortened: the whole product takes 2.60 / 2.34 ms
+// there since, so that line could lie lower.
 //
 // In spaces of up to kCoreFewStates states a task is one to four subtiles and an
 // item costs its set-up, whatever it gathers, while the jump kernel pays per row:

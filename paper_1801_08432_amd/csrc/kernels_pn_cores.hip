@@ -10,13 +10,13 @@
 // one-body-jump form (k_pn, k_pn2) gathers its contracted tile N (N_s - N + 1)
 // times, and the dense matrices cover the pairs of a class (1.8 to 2.4 times the
 // useful multiply-adds in 20 states) instead of the labels of an operator class
-// (6.2 times). pn part at 5p5n in 20 states, dim 18.6 M: float32 2.84 -> 1.64 ms,
-// float64 6.90 -> 2.39 ms (4p4n: 0.377 -> 0.186 and 0.662 -> 0.265 ms). What bounds it (float32,
-// with parts taken out): 0.25 ms to set up and write out the items, one
-// workgroup per CU, 0.3 ms to load the operands of the tasks, and subtiles that
-// issue 41% of the time to the vector and 31% to the matrix units; without the
-// loads of x and its codes it still runs at 1.49 ms, without the matrix
-// instructions at 1.35 ms.
+// (6.2 times). pn part at 5p5n in 20 states, dim 18.6 M: float32 2.84 -> 1.57 ms,
+// float64 6.90 -> 2.34 ms (4p4n: 0.377 -> 0.184 and 0.662 -> 0.260 ms). What bounds it (float32):
+// 0.2 ms to set up and write out the items, one workgroup per CU, 0.3 ms to
+// load the operands of the tasks, and subtiles that issue 31% of the time to the
+// vector and 34% to the matrix units. With parts taken out, when the whole took
+// 1.64 ms (0.25 of it set-up): 1.49 without the loads of x and its codes, 1.35
+// without the matrix instructions.
 #include "tiled_common.h"
 
 namespace fotci {
@@ -50,8 +50,10 @@ struct CoreLds {
 // [s0, s1) of a neutron core group. x of the next subtile and the codes of the
 // one after it are in flight while a subtile is worked on. Results are added to
 // the rows with LDS float64 atomics (8 cycles a wave on gfx950, where a float32
-// atomic takes 192 and a read and write 10), also in float32, where the float64
-// sum of a row element's few addends is exact, so their order does not matter.
+// atomic takes 192 and a read and write 10), also in float32, where the waves'
+// order shows in the last bit of the float64 sum at most, and only if a row
+// element's addends span 29 binary orders or more: float32 products are the same
+// bits from run to run almost always, but not by construction.
 template <typename T, int KST>
 __device__ __forceinline__ void core_pass(const CoreLds &S, const uint32_t *kl, const uint32_t *ml, int nk, int nm, int n,
                                           unsigned pv, const int32_t *pab, unsigned wbytes, int wpad, int s0,
@@ -376,8 +378,9 @@ void launch_cores(const fotci_ham *h, int nb, const T *x, T *slots, hipStream_t 
     };
     // Workgroups of four waves where their rows leave room for as many of them
     // as the registers do (three float32, two float64), else one of all the
-    // waves a CU takes: small sectors have few tasks per item (float32 pn part at
-    // 4p4n in 20 states: 0.23 ms with four waves, 0.29 with six).
+    // waves a CU takes: small sectors have few tasks per item (pn part at 4p4n in
+    // 20 states, four waves against all: float32 0.184 / 0.253 ms, float64 0.260 /
+    // 0.310; 3p4n, float32 0.049 / 0.063).
     constexpr int kMost = core_threads<T>();
     const int threads = bytes(256) * (kMost / 256) <= 156 * 1024 ? 256 : kMost;
     hipLaunchKernelGGL(k_pn_core<T>, dim3(grid), dim3(threads), bytes(threads), st, h->dev, h->dev_core, h->dev_core.items,
