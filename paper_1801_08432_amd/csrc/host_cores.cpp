@@ -18,8 +18,6 @@ namespace {
 inline bool odd_below(uint32_t m, int i) { return __builtin_popcount(m & ((1u << i) - 1u)) & 1; }
 
 constexpr int kCoreVjpTasks = 1536;   // three rounds of two workgroups a CU
-constexpr int kCoreFewStates = 12;    // see apply_on_cores
-constexpr double kCoreFewLine = 1.2;
 
 struct Cores {
     std::vector<uint32_t> mask;              // grouped by (2M, parity), ascending inside a group
@@ -213,28 +211,27 @@ void build_label_tasks(HostCore &t, int nu) {
 // before the items' set-up was shortened: the whole product takes 2.60 / 2.34 ms
 // there since, so that line could lie lower.
 //
-// In spaces of up to kCoreFewStates states a task is one to four subtiles and an
-// item costs its set-up, whatever it gathers, while the jump kernel pays per row:
-// there the ratio is divided by the items per row, and by what a last round of
-// workgroups leaves idle. float64 takes the cores from kCoreFewLine on or where all
-// items run at once; float32, three workgroups a CU and cheaper registers, as
-// elsewhere. Measured, us of a product (12 states, float64, jumps / cores), by
-// the quotient: 49.8 / 68.6 at 0.40 (8p4n, blocks of 2), 44.7 / 51.6 at 0.59
-// (7p5n), 46.3 / 51.2 at 0.80 (6p5n), 69.8 / 72.1 at 1.0 (4p3n, blocks of 4), 41.9 /
-// 44.3 at 1.01 (6p4n), 80.1 / 72.2 at 1.26 (5p6n, blocks of 2); one round: 38.3 /
-// 32.7 (4p4n). In 16 and more states the cores win from quotients of 0.5 on (18
-// states, 8p4n: 4.77 / 3.82 ms).
+// With few states a task is a few subtiles and an item costs its set-up, whatever
+// it gathers, while the jump kernel pays per row: float64 products also need the
+// ratio, divided by the items per row and times the share of a last round of
+// workgroups that is not idle, to reach 1.2 (12 / N_s)^3, unless all items run
+// at once (the line from 2000 products in spaces of 8 to 20 states, timed both ways: 47 of
+// them are left more than 3% slower than by jumps, where the ratio alone left 244;
+// 15 lose as much). float32, three workgroups a CU and cheaper registers, goes by the
+// ratio. us of a product, jumps / cores, by the quotient: 12 states: 49.8 / 68.6
+// at 0.40 (8p4n, blocks of 2), 46.3 / 51.2 at 0.80 (6p5n), 69.8 / 72.1 at 1.0 (4p3n,
+// blocks of 4), 80.1 / 72.2 at 1.26 (5p6n, blocks of 2), one round 38.3 / 32.7 (4p4n); 14
+// states: 128 / 157 at 0.52 (9p5n), 97 / 114 at 0.63 (6p3n), 130 / 110 at 1.16 (4p5n, blocks
+// of 2); 16 states: 503 / 401 at 0.80 (6p4n); 18 states: 4767 / 3821 at 0.54 (8p4n).
 bool apply_on_cores(const fotci_ham *h, int mode, int nb) {
     const double ns = h->j->ns, Z = h->j->b->p.n, N = h->j->b->n.n, open = ns - N + 1;
     const double groups = std::ceil((ns - Z + 1) / kCoreStates);
     const double ratio = N * open / (Z * N * ns / open * groups);
     if (ratio < (mode == FOTCI_MODE_F64 ? 0.75 : 1.0)) return false;
-    if (mode == FOTCI_MODE_F64 && ns <= kCoreFewStates) {
-        const double cores = (double)h->hc.u_mask.size() * groups, rows = (double)h->j->b->p.sd.size();
-        const double rounds = cores * nb / 512.0;   // of four-wave workgroups, two a CU
-        if (rounds > 1.0 && ratio * rows / cores * (rounds / std::ceil(rounds)) < kCoreFewLine) return false;
-    }
-    return true;
+    if (mode != FOTCI_MODE_F64) return true;
+    const double items = (double)h->hc.u_mask.size() * groups, rows = (double)h->j->b->p.sd.size();
+    const double rounds = items * nb / 512.0;   // of four-wave workgroups, two a CU
+    return rounds <= 1.0 || ratio * rows / items * (rounds / std::ceil(rounds)) >= 1.2 * std::pow(12.0 / ns, 3);
 }
 
 // Per element of g the cores gather Z N pairs, of which a share (N_s - N + 1) /

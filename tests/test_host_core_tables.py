@@ -10,7 +10,7 @@ def _ham(two_j, Z, N):
     return fotci.Hamiltonian(fotci.Jumps(b), inter)
 
 
-# Measured in 12 states, microseconds of one product by jumps and by cores (float64 unless said otherwise)
+# Measured, microseconds of one product by jumps and by cores
 @pytest.mark.parametrize("Z,N,mode,n_block,cores", [
     (8, 4, "f64", 1, False),   # 39.0 / 42.3
     (8, 4, "f64", 2, False),   # 49.8 / 68.6
@@ -26,7 +26,25 @@ def _ham(two_j, Z, N):
     (7, 3, "f32", 8, True),    # 175 / 148
     (6, 6, "f32", 1, False),
 ])
-def test_small_spaces_take_the_faster_kernel(Z, N, mode, n_block, cores):
-    ham = _ham((1, 3, 5), Z, N)
+def test_twelve_states_take_the_faster_kernel(Z, N, mode, n_block, cores):
+    _check((1, 3, 5), Z, N, mode, n_block, cores)
+
+
+@pytest.mark.parametrize("two_j,Z,N,mode,n_block,cores", [
+    ((7,), 5, 2, "f64", 8, False),       # 34.0 / 37.0
+    ((3, 5), 7, 3, "f64", 8, False),     # 55.6 / 81.9
+    ((1, 3, 7), 6, 3, "f64", 1, False),  # 97 / 114
+    ((1, 3, 7), 9, 5, "f64", 4, False),  # 445 / 553
+    ((1, 3, 7), 4, 5, "f64", 2, True),   # 130 / 110
+    ((1, 5, 7), 6, 4, "f64", 1, True),   # 503 / 401
+    ((3, 5, 7), 3, 3, "f64", 1, True),   # 55 / 37
+    ((1, 3, 5, 7), 3, 4, "f64", 1, True),
+])
+def test_other_spaces_take_the_faster_kernel(two_j, Z, N, mode, n_block, cores):
+    _check(two_j, Z, N, mode, n_block, cores)
+
+
+def _check(two_j, Z, N, mode, n_block, cores):
+    ham = _ham(two_j, Z, N)
     need = fotci.lib().fotci_apply_work_bytes(ham._h, fotci.MODES[mode], n_block)
     assert need == (ham.dim * n_block * (8 if mode == "f64" else 4) * Z if cores else 0)
