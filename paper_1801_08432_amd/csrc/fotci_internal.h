@@ -153,7 +153,7 @@ struct alignas(4) EllE64 {
 // For a proton core u and a pair class the neutron cores that complete the
 // basis quantum numbers are one neutron core group.
 constexpr int kCoreMinShift = 2, kCoreMaxShift = 6;   // byte offset = column << shift: log2(element size * vectors)
-constexpr int kObdCores = 32;       // proton cores of a density task
+constexpr int kObdCores = 32;       // proton cores of a density task at most
 constexpr int kObdRows = 256;       // proton rows of one
 constexpr uint32_t kCoreNoRow = 0xffffffffu;
 constexpr int kCoreMaxPc = 64;      // pair classes
@@ -185,9 +185,9 @@ struct DevCore {
     // class of states fills up to a basis sector's neutron sector, tasks
     const int32_t *sp_ptr, *sp_state;
     const int32_t *ow_of;      // [n_sectors * n_sp], -1: none
-    const int32_t *op_tasks;   // {class, block, first proton core}
+    const int32_t *op_tasks;   // {class, block, first, end proton core}
     const int32_t *on_tasks;   // {class, block, basis sector, first core, first row}
-    int32_t n_sp, n_u;
+    int32_t n_sp;
     const int32_t *items;      // work items {proton core, mask of the added states a}
     int32_t n_pc, n_w_code, w_null, n_v, ns;   // w_null: first of a run of null codes as long as the largest group
 };

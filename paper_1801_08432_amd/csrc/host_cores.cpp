@@ -323,7 +323,9 @@ void build_core_tables(fotci_ham *h) {
     // entries per task (b block | d block << 4).
     std::map<std::pair<int, int>, std::vector<int>> sps;
     for (int a = 0; a < ns; ++a) sps[{ms[a].two_m, ms[a].parity}].push_back(a);
-    const int n_sp = (int)sps.size(), n_s = (int)b->sectors.size();
+    const int n_sp = (int)sps.size(), n_s = (int)b->sectors.size(), n_u = (int)U.mask.size();
+    // a core a wave where there are few (a wave takes its cores one after another)
+    const int per = std::min(kObdCores, std::max(4, n_u / 128));
     t.sp_ptr.assign(1, 0);
     t.ow_of.assign((size_t)n_s * n_sp, -1);
     int cls = 0;
@@ -339,7 +341,7 @@ void build_core_tables(fotci_ham *h) {
         for (int bb = 0; bb < nblk; ++bb)
             for (int db = 0; db < nblk; ++db) {
                 const int blk = bb | (db << 4);
-                for (int u = 0; u < (int)U.mask.size(); u += kObdCores) t.op_tasks.insert(t.op_tasks.end(), {cls, blk, u});
+                for (int u = 0; u < n_u; u += per) t.op_tasks.insert(t.op_tasks.end(), {cls, blk, u, std::min(u + per, n_u)});
                 for (int s = 0; s < n_s; ++s) {
                     const int w = t.ow_of[(size_t)s * n_sp + cls];
                     if (w < 0) continue;

@@ -585,7 +585,6 @@ std::vector<Item> items(fotci_ham *h) {
     add(hc.u_base.data(), hc.u_base.size() * 4, &dc.u_base);
     add(hc.v_tasks.data(), hc.v_tasks.size() * 4, &dc.v_tasks);
     dc.n_sp = (int32_t)hc.sp_ptr.size() - 1;
-    dc.n_u = (int32_t)hc.u_mask.size();
     add(hc.sp_ptr.data(), hc.sp_ptr.size() * 4, &dc.sp_ptr);
     add(hc.sp_state.data(), hc.sp_state.size() * 4, &dc.sp_state);
     add(hc.ow_of.data(), hc.ow_of.size() * 4, &dc.ow_of);

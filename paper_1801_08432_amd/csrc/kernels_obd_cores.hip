@@ -68,11 +68,11 @@ __device__ __forceinline__ void oc_states(const DevCore &C, int cls, int blk, in
     }
 }
 
-// task {class, block, first proton core}: kObdCores cores, the waves in turn
+// task {class, block, first, end proton core}: the waves take the cores in turn
 __global__ __launch_bounds__(kOcThreads) void k_obd_p(DevHam P, DevCore C, const double *__restrict__ x,
                                                       const double *__restrict__ g, double *rho) {
     __shared__ double lds[kOcWaves][16];
-    const int32_t *t = C.op_tasks + 3 * (int64_t)blockIdx.x;
+    const int32_t *t = C.op_tasks + 4 * (int64_t)blockIdx.x;
     const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int b[4], d[4];
     oc_states(C, t[0], t[1], b, d);
@@ -84,7 +84,7 @@ __global__ __launch_bounds__(kOcThreads) void k_obd_p(DevHam P, DevCore C, const
     for (int i = 0; i < 4; ++i)
 #pragma unroll
         for (int j = 0; j < 4; ++j) acc[i][j] = 0.0;
-    const int u1 = min(t[2] + kObdCores, C.n_u);
+    const int u1 = t[3];
     for (int u = t[2] + wid; u < u1; u += kOcWaves) {
         // rows of the states, all in one sector: their common length
         uint32_t rb[4], rd[4];
@@ -192,7 +192,7 @@ __global__ __launch_bounds__(kOcThreads) void k_obd_n(DevHam P, DevCore C, const
 }  // namespace
 
 void launch_obd_cores(const fotci_ham *h, const double *g, const double *x, double *rho_p, double *rho_n, void *stream) {
-    const int np = (int)(h->hc.op_tasks.size() / 3), nn = (int)(h->hc.on_tasks.size() / 5);
+    const int np = (int)(h->hc.op_tasks.size() / 4), nn = (int)(h->hc.on_tasks.size() / 5);
     if (rho_p && np)
         hipLaunchKernelGGL(k_obd_p, dim3(np), dim3(kOcThreads), 0, (hipStream_t)stream, h->dev, h->dev_core, x, g, rho_p);
     if (rho_n && nn)

@@ -220,12 +220,19 @@ static void check(const Shape &sh) {
         }
         CHECK(close(got, dv));
     }
-    // one-body densities
+    // one-body densities: every core once a class and block
+    std::map<std::pair<int, int>, int> next;
+    for (size_t k = 0; k < t.op_tasks.size(); k += 4) {
+        int &from = next[{t.op_tasks[k], t.op_tasks[k + 1]}];
+        CHECK(t.op_tasks[k + 2] == from && t.op_tasks[k + 3] > from && t.op_tasks[k + 3] - from <= kObdCores);
+        from = t.op_tasks[k + 3];
+    }
+    for (auto &n : next) CHECK(n.second == n_u);
     std::vector<double> gp(ns2, 0.0), gn(ns2, 0.0);
     const int n_sp = (int)t.sp_ptr.size() - 1;
     auto state = [&](int c, int i) { return t.sp_ptr[c] + i < t.sp_ptr[c + 1] ? t.sp_state[t.sp_ptr[c] + i] : -1; };
-    for (size_t k = 0; k < t.op_tasks.size(); k += 3)
-        for (int u = t.op_tasks[k + 2]; u < std::min(t.op_tasks[k + 2] + kObdCores, n_u); ++u)
+    for (size_t k = 0; k < t.op_tasks.size(); k += 4)
+        for (int u = t.op_tasks[k + 2]; u < t.op_tasks[k + 3]; ++u)
             for (int i = 0; i < 4; ++i)
                 for (int jj = 0; jj < 4; ++jj) {
                     const int bb = state(t.op_tasks[k], 4 * (t.op_tasks[k + 1] & 15) + i);
