@@ -325,8 +325,10 @@ class Hamiltonian:
                      v_pn=torch.zeros(ns * ns, ns * ns, dtype=torch.float64, device=dev))
         dx = torch.empty_like(x) if want_dx else None
         fn = lib().fotci_apply_H_vjp_static if static_scratch else lib().fotci_apply_H_vjp
-        # dx = H g as an apply of its own, which may use work memory
-        split = want_dx and not static_scratch and lib().fotci_apply_work_bytes(self._h, MODE_F64, 1) > 0
+        # dx = H g as an apply of its own, which may use work memory; its allocation and call take longer on the host
+        # than they save where that is a few KiB (adjoint of one proton and one neutron, dim 28: 58 us in one call, 65 in
+        # two; one proton and three neutrons, 3 KiB: 85 and 68)
+        split = want_dx and not static_scratch and lib().fotci_apply_work_bytes(self._h, MODE_F64, 1) > 2048
         if split:
             self._apply(MODE_F64, 1, g, dx, stream)
         _check(fn(self._h, _dev_ptr(x), _dev_ptr(g), None if split else _dev_ptr(dx), _dev_ptr(grads["eps_p"]),

@@ -226,3 +226,18 @@ def test_a_stream_may_be_any_object_with_its_handle():
     h.apply(x, y, stream=s)
     torch.cuda.synchronize()
     assert float((y - want).norm()) <= 1e-13 * float(want.norm())
+
+
+@pytest.mark.parametrize("Z,N,two_M", [(1, 1, 0), (2, 1, 1), (1, 3, 0)])
+def test_adjoint_of_tiny_bases(Z, N, two_M):
+    """dx as an apply of its own, and (work memory of 2 KiB or less) in the adjoint's call."""
+    inter, rng = inputs.random_interaction((1, 3, 5), 79)
+    h = fotci.Hamiltonian.build((1, 3, 5), Z, N, two_M, inter, device=DEV)
+    prep = fast.Prepared(ob.build_basis((1, 3, 5), Z, N, two_M))
+    x, g = rng.standard_normal(h.dim), rng.standard_normal(h.dim)
+    dx, grads = h.vjp(torch.from_numpy(x).to(DEV), torch.from_numpy(g).to(DEV))
+    assert _rel(dx.cpu().numpy(), fast.apply_h(prep, inter, g)) <= 1e-13
+    ref = fast.densities(prep, g, x)
+    for k in ("v_pp", "v_nn", "v_pn", "eps_p", "eps_n"):
+        r = np.asarray(ref["d_" + k]).ravel()
+        assert np.linalg.norm(grads[k].cpu().numpy().ravel() - r) <= 1e-13 * max(np.linalg.norm(r), 1.0), k
