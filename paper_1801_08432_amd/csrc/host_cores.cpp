@@ -324,8 +324,10 @@ void build_core_tables(fotci_ham *h) {
     std::map<std::pair<int, int>, std::vector<int>> sps;
     for (int a = 0; a < ns; ++a) sps[{ms[a].two_m, ms[a].parity}].push_back(a);
     const int n_sp = (int)sps.size(), n_s = (int)b->sectors.size(), n_u = (int)U.mask.size();
-    // a core a wave where there are few (a wave takes its cores one after another)
-    const int per = std::min(kObdCores, std::max(4, n_u / 128));
+    // A wave takes its cores one after another, so one each where there are few; but every task adds to the same
+    // entries. Densities in us with tasks of 32 cores, of n_u / 64, of n_u / 128: 68 / 47 / 47 (pf 3p4n, 190 cores), 36 / 35 / 40
+    // (pf 4p1n, 1140), 79 / 72 / 71 (pf 4p4n, 1140), 22 / 19 / 19 (j = 7/2 4p4n, 56).
+    const int per = std::min(kObdCores, std::max(4, n_u / 64));
     t.sp_ptr.assign(1, 0);
     t.ow_of.assign((size_t)n_s * n_sp, -1);
     int cls = 0;
