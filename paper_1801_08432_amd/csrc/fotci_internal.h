@@ -365,7 +365,7 @@ struct fotci_ham {
         void record(std::initializer_list<const char *> parts, bool pn_first) {
             n_kernels = 0;
             for (const char *p : parts) names[n_kernels++] = p;
-            order[calls++] = {n_kernels, pn_first};
+            if (calls < max_calls) order[calls++] = {n_kernels, pn_first};
         }
     };
     mutable Profile prof;

@@ -256,9 +256,8 @@ int64_t apply_work_bytes(const fotci_ham *h, int mode, int nb) {
 
 // Tables of the proton and neutron cores and of the densities, which every basis
 // uses, and those of the products and the label densities where these run on
-// the cores (14p18n in 20 states, which has neither: 174 of the 444 ms that all
-// of them took went into items, tasks and copies of the code table, and into
-// searching sorted lists).
+// the cores (fotci_set_interaction at 14p18n in 20 states, which has neither: 350
+// ms with all of them built and searched for in sorted lists, 165 ms so).
 void build_core_tables(fotci_ham *h) {
     const fotci_basis *b = h->j->b;
     const auto &ms = b->ms;
